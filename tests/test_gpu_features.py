@@ -61,6 +61,41 @@ def test_lfr_features_bit_exact(offset, bf16):
         np.testing.assert_array_equal(x.cpu().numpy().view(np.uint32), ref.view(np.uint32))
 
 
+@pytest.mark.parametrize("raw_dim", [1, 21, 22, 40])
+def test_lfr_features_chunk_edges_and_special_values(raw_dim):
+    # 32-frame chunks and 64-dimension groups with remainders on both sides,
+    # and raw values (zeros, infinities, NaN, the largest and the smallest)
+    # whose quotients leave the range the corrected division covers
+    T = np.array([97, 96, 65, 64, 63, 33, 32, 31, 2, 1, 1, 0], np.int32)
+    U = 3 * T + np.arange(len(T), dtype=np.int32) % 3
+    D = 3 * raw_dim
+    rng = np.random.default_rng(raw_dim)
+    raw = rng.normal(2.0, 3.0, (int(U.sum()), raw_dim)).astype(np.float32)
+    special = np.array([0.0, -0.0, np.inf, -np.inf, np.nan, 3e38, -3e38, 1e-45, -1e-38], np.float32)
+    at = rng.integers(0, raw.size, 40)
+    raw.reshape(-1)[at] = special[np.arange(40) % len(special)]
+    raw[:3 * T[0]] = 0.0  # a constant utterance: every difference is zero
+    mean = rng.normal(0, 0.5, D).astype(np.float32)
+    mean[0] = 0.0
+    std = rng.uniform(0.5, 2.0, D).astype(np.float32)
+    std[-1] = 1e-45
+    counts, offs = oracle.batch_schedule(int(T[0]), len(T), T)
+    ref = np.zeros((int(offs[-1]), D))
+    r0 = 0
+    with np.errstate(all="ignore"):
+        for b in range(len(T)):
+            f = oracle.lfr_features(raw[r0:r0 + U[b]], mean, std, 3, 3, 0)
+            ref[offs[:f.shape[0]].astype(int) + b] = f
+            r0 += int(U[b])
+        ref = ref.astype(np.float32)
+    x = torch.zeros(ref.shape, dtype=torch.float32, device="cuda")
+    am.lfr_features(U, to_dev(raw), to_dev(mean), to_dev(std), x)
+    got = x.cpu().numpy()
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+    ok = ~np.isnan(ref)
+    np.testing.assert_array_equal(got.view(np.uint32)[ok], ref.view(np.uint32)[ok])
+
+
 @pytest.mark.parametrize("lengths_kind", [None, "varlen"])
 @pytest.mark.parametrize("delay", [0, 1, 3])
 def test_delay_targets_bit_exact(lengths_kind, delay):
