@@ -95,6 +95,7 @@ hipError_t lstm_cell_bwd(const float* dhrec, int splits, const LstmBwdStep& a, h
 // sorted lengths (B <= 1024), else every sequence has T frames.
 struct PersistSchedule {
   int T, B, N;
+  int first;  // first sequence of this launch (XCD-local kernels: a round of the batch)
   int varlen;
   uint16_t lens[1024];
 };
@@ -133,7 +134,12 @@ struct XcdSync {
   int fenced;  // nonzero: exchange with release/acquire fences even when every
                // block is found on one XCD (AM_XCD_FENCED=1, for tests)
 };
-bool lstm_xcd_instantiated(bool forward, int hidden, int B);
+// Words between the sync slots of consecutive rounds of a recurrence, and the
+// most rounds (launches of 128 or 256 sequences) one takes.  More rounds are
+// left to the per-step kernels, whose products fill the chip by then.
+constexpr int XCD_SYNC_WORDS = 8192 / 4;
+constexpr int XCD_MAX_ROUNDS = 4;
+bool lstm_xcd_instantiated(int hidden, int B);
 // Launch of a grid that the caller has checked fits on the device at once
 // (occupancy x CUs).  With AM_COOPERATIVE=1 in the environment it goes
 // through the cooperative launch (which guarantees co-residency but adds

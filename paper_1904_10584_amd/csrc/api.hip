@@ -206,7 +206,8 @@ bool device_persistent_enabled() {
 
 // Scratch of the persistent kernels: the sync area at offset 0 of the
 // workspace, one SYNC_BYTES slot per recurrence launch of a pass (each
-// launch's step flags and XCC ids), so that one clear at the
+// launch's step flags and XCC ids; several per layer where the sequences go
+// in rounds), so that one clear at the
 // start of a pass serves all its launches instead of one small clear kernel
 // before each.  The last word of slot 0 is the barrier time-out flag of
 // every launch, zeroed once per forward pass and only ever set afterwards,
@@ -217,7 +218,17 @@ constexpr int64_t SYNC_BYTES = 8192;
 // the 256 CUs with the 48 tiles of B = 512, H = 1536)
 constexpr int STEP_SPLITS = 5;
 constexpr int64_t SYNC_STICKY_WORD = SYNC_BYTES / 4 - 1;
-void* sync_slot(void* area, int k) { return static_cast<char*>(area) + (int64_t)k * SYNC_BYTES; }
+static_assert(am::XCD_SYNC_WORDS * 4 == SYNC_BYTES, "a round's slot follows the one before");
+// Slots of one recurrence: one for each round of sequences it may be run in
+// (a round holds at least 128).
+int sync_rounds(int64_t B) {
+  const int64_t r = (B + 127) / 128;
+  return (int)(r < 1 ? 1 : r > am::XCD_MAX_ROUNDS ? am::XCD_MAX_ROUNDS : r);
+}
+// First slot of recurrence k of a pass over B sequences.
+void* sync_slot(void* area, int k, int64_t B) {
+  return static_cast<char*>(area) + (int64_t)k * sync_rounds(B) * SYNC_BYTES;
+}
 int* sync_err(void* area) { return static_cast<int*>(area) + SYNC_STICKY_WORD; }
 am::XcdSync xcd_sync(void* slot, int* err) {
   unsigned* u = static_cast<unsigned*>(slot);
@@ -234,14 +245,14 @@ static_assert(512 + 512 <= SYNC_STICKY_WORD, "a slot holds the flag and XCC line
 // Whether the XCD-local kernels take this layer's recurrence: bf16, the
 // shape instantiated, and (variable lengths) T within the schedule's 16-bit
 // lengths.
-bool xcd_shape(bool forward, bool bf, int64_t H, int T, int B, bool varlen) {
-  return bf && xcd_enabled() && am::lstm_xcd_instantiated(forward, (int)H, B) &&
+bool xcd_shape(bool bf, int64_t H, int T, int B, bool varlen) {
+  return bf && xcd_enabled() && am::lstm_xcd_instantiated((int)H, B) &&
          (!varlen || T <= 65535);
 }
-bool xcd_path(bool forward, bool bf, int64_t H, const Schedule& sc) {
+bool xcd_path(bool bf, int64_t H, const Schedule& sc) {
   bool varlen = false;
   for (int b = 0; b < sc.B && !varlen; ++b) varlen = sc.lens[b] != sc.T;
-  return xcd_shape(forward, bf, H, sc.T, sc.B, varlen);
+  return xcd_shape(bf, H, sc.T, sc.B, varlen);
 }
 
 // AM_DEBUG=1 in the environment: entry points that consume indices held in
@@ -256,6 +267,7 @@ am::PersistSchedule persist_schedule(const Schedule& sc) {
   ps.T = sc.T;
   ps.B = sc.B;
   ps.N = (int)sc.N;
+  ps.first = 0;
   ps.varlen = 0;
   for (int b = 0; b < sc.B; ++b)
     if (sc.lens[b] != sc.T) ps.varlen = 1;
@@ -281,7 +293,7 @@ WsLayout ws_layout(const am_model* m, int64_t B, int64_t N) {
   auto take = [&](int64_t bytes) { int64_t at = pos; pos += align256(bytes); return at; };
   // step-barrier scratch of the persistent kernels (a slot per layer and
   // direction of the pass) and the time-out flag
-  w.sync = take(2 * L * SYNC_BYTES);
+  w.sync = take(2 * L * sync_rounds(B) * SYNC_BYTES);
   for (int l = 0; l < L; ++l) {
     w.h.push_back(take(N * H * e));
     w.hs.push_back(take(N * H * e));
@@ -368,7 +380,7 @@ am_status forward_recurrence(const FwdLayer& f, const Schedule& sc, bool bf, int
     const double flops = 2.0 * sc.N * G * H;
     const double bytes = (double)sc.N * (G * e * 2 + H * (2 * e + 4)) + (double)G * H * e;
     bool used = false;
-    if (xcd_path(true, bf, H, sc)) {
+    if (xcd_path(bf, H, sc)) {
       Timed tm(AM_K_LSTM_FWD, s, flops, bytes);
       AM_TRY(hip_check(am::lstm_fwd_xcd_launch(pa, ps, xcd_sync(f.sync, f.err), s, &used),
                        "lstm forward layer (xcd)"));
@@ -491,7 +503,7 @@ TeacherWs teacher_ws_layout(const am_model* m, int64_t T, int64_t B, int64_t N) 
   const int64_t Dmax = m->input_dim > 2 * H ? m->input_dim : 2 * H;
   int64_t pos = 0;
   auto take = [&](int64_t bytes) { int64_t at = pos; pos += align256(bytes); return at; };
-  w.sync = take(2 * m->layers * SYNC_BYTES);  // a slot per layer and direction
+  w.sync = take(2 * m->layers * sync_rounds(B) * SYNC_BYTES);  // a slot per layer and direction
   w.offs = take((T + 1) * 8);
   w.lens = take(B * 4);
   w.cat0 = take(N * 2 * H * e);
@@ -608,7 +620,7 @@ int32_t am_recurrence_path(const am_model* m, int32_t T, int32_t B, int32_t varl
   if (check_model(m) != AM_OK || T < 0 || B < 1) return -1;
   const bool bf = m->dtype == AM_BF16, fw = forward != 0;
   if (!persistent_enabled()) return AM_PATH_STEP;
-  if (xcd_shape(fw, bf, m->hidden, T, B, varlen != 0)) return AM_PATH_XCD;
+  if (xcd_shape(bf, m->hidden, T, B, varlen != 0)) return AM_PATH_XCD;
   if (device_persistent_enabled() && am::lstm_persistent_fits(fw, m->hidden, B, bf, T))
     return AM_PATH_DEVICE;
   return AM_PATH_STEP;
@@ -863,7 +875,7 @@ am_status blstm_teacher_forward(const am_model* m, const void* params, const voi
     AM_TRY(hip_check(am::schedule_tables(st, s), "schedule tables"));
   }
   AM_TRY(hip_check(am::fill_zero2(at<float>(ws, w.c0), B * H, at<float>(ws, w.sync),
-                                  2 * L * SYNC_BYTES / 4, s), "c0 and sync clear"));
+                                  2 * L * sync_rounds(B) * SYNC_BYTES / 4, s), "c0 and sync clear"));
   auto gather = [&](const void* src, int64_t src_ld, void* dst, int64_t dst_ld, int64_t col,
                     int width, bool reverse) {
     am::GatherRows g;
@@ -898,7 +910,7 @@ am_status blstm_teacher_forward(const am_model* m, const void* params, const voi
       f.Hs = at<void>(ws, w.hs);
       f.C = at<float>(ws, w.c);
       f.G = at<void>(ws, w.g);
-      f.sync = sync_slot(at<void>(ws, w.sync), k);
+      f.sync = sync_slot(at<void>(ws, w.sync), k, B);
       f.err = sync_err(at<void>(ws, w.sync));
       f.pre = at<float>(ws, w.pre);
       AM_TRY(forward_recurrence(f, sc, bf, H, s));
@@ -1000,7 +1012,7 @@ am_status lstm_am_forward(const am_model* m, const void* params, const void* x,
     if (h0) AM_TRY(hip_check(am::convert_rows(h0, at<void>(ws, w.h0), L * B * H, bf, s), "h0 convert"));
     // a new forward + backward pair: every slot of the sync area and the
     // barrier time-out flag (and a zero initial cell state, in the same launch)
-    AM_TRY(hip_check(am::fill_zero2(at<float>(ws, w.sync), 2 * L * SYNC_BYTES / 4, c0w,
+    AM_TRY(hip_check(am::fill_zero2(at<float>(ws, w.sync), 2 * L * sync_rounds(B) * SYNC_BYTES / 4, c0w,
                                     c0 ? 0 : L * B * H, s), "sync and c0 clear"));
   }
 
@@ -1020,7 +1032,7 @@ am_status lstm_am_forward(const am_model* m, const void* params, const void* x,
     f.Hs = at<void>(ws, w.hs[l]);
     f.C = at<float>(ws, w.c[l]);
     f.G = at<void>(ws, w.g[l]);
-    f.sync = sync_slot(at<void>(ws, w.sync), l);
+    f.sync = sync_slot(at<void>(ws, w.sync), l, B);
     f.err = sync_err(at<void>(ws, w.sync));
     f.pre = at<float>(ws, w.pre);
     AM_TRY(forward_recurrence(f, sc, bf, H, s));
@@ -1078,8 +1090,8 @@ am_status lstm_am_backward(const am_model* m, const void* params, const void* x,
   const char* P8 = static_cast<const char*>(params);
   float* skws = at<float>(ws, w.splitk);
   // the backward launches' slots of the sync area (not slot 0's time-out flag)
-  AM_TRY(hip_check(am::fill_zero(static_cast<float*>(sync_slot(at<void>(ws, w.sync), (int)L)),
-                                 L * SYNC_BYTES / 4, s), "sync clear"));
+  AM_TRY(hip_check(am::fill_zero(static_cast<float*>(sync_slot(at<void>(ws, w.sync), (int)L, B)),
+                                 L * sync_rounds(B) * SYNC_BYTES / 4, s), "sync clear"));
 
   // output layer: dWo = dZ^T H_top and dbo = column sums of dZ (one pass),
   // then dH_top = dZ Wo
@@ -1098,7 +1110,7 @@ am_status lstm_am_backward(const am_model* m, const void* params, const void* x,
   // the XCD-local recurrences read W_h^T: every layer's, transposed up front
   // in one launch (falls back to one transpose per layer below)
   bool wht_ready = false;
-  if (sc.N > 0 && persistent_enabled() && xcd_path(false, bf, H, sc)) {
+  if (sc.N > 0 && persistent_enabled() && xcd_path(bf, H, sc)) {
     Timed tm(AM_K_MISC, s, 0.0, 2.0 * L * G * H * e);
     wht_ready = true;
     for (int l0 = 0; l0 < L && wht_ready; l0 += am::TransposeBatch::MAX) {
@@ -1129,14 +1141,14 @@ am_status lstm_am_backward(const am_model* m, const void* params, const void* x,
       pa.C = Cl;
       pa.c0 = at<float>(ws, w.c0) + (int64_t)l * B * H;
       pa.dA = dA;
-      void* slot = sync_slot(at<void>(ws, w.sync), L + l);
+      void* slot = sync_slot(at<void>(ws, w.sync), (int)L + l, B);
       pa.counters = static_cast<unsigned*>(slot);
       pa.err = sync_err(at<void>(ws, w.sync));
       pa.hidden = (int)H;
       const am::PersistSchedule ps = persist_schedule(sc);
       const double flops = 2.0 * (sc.N - sc.counts[0]) * G * H;
       const double bytes = (double)sc.N * (G * e * 2 + H * (e + 8)) + (double)G * H * e;
-      if (xcd_path(false, bf, H, sc)) {
+      if (xcd_path(bf, H, sc)) {
         if (!wht_ready) {
           Timed tm(AM_K_MISC, s, 0.0, 2.0 * G * H * e);
           AM_TRY(hip_check(am::transpose(P8 + po.wh[l] * e, WhT, (int)G, (int)H, bf, s), "Wh transpose"));

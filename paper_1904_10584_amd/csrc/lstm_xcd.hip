@@ -28,6 +28,7 @@
 // pre-activations of one (sequence, unit).  The backward product keeps the
 // U columns of W_h in registers too.
 #include <cstdlib>
+#include <type_traits>
 
 #include "am_device.h"
 #include "am_internal.h"
@@ -195,7 +196,7 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
   const int ntiles = MT * (U / 4);
   const int members = H / U;
   const int blk = xcd_block(members), us = (blockIdx.x / NX) % members;
-  const int b0 = blk * RB, j0 = us * U;
+  const int b0 = ps.first + blk * RB, j0 = us * U;
   const int mw = g % MT;
   const int CSB = U * 4 + 16, HSB = U * 2 + 16, GSB = U * 8 + 16;  // staged row strides
   unsigned char* stH = stC + RB * CSB;
@@ -321,6 +322,7 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
         Frag<bf16_t> af[AB];
 #pragma unroll
         for (int s = 0; s < AB; ++s) {
+          if (s0 + s >= KH) continue;  // (compile time: the last batch may be shorter)
           const int c = (kh * KH + s0 + s) * 4 + (lane >> 4);
           af[s] = *reinterpret_cast<const Frag<bf16_t>*>(
               hl + ((c >> 3) * RB + r) * 64 + (((c & 7) ^ (r & 7)) << 3));
@@ -329,9 +331,11 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
         // unconditional: a tile past the last holds tile 0's weights and its
         // result is never used (a guard here would branch around each MFMA)
 #pragma unroll
-        for (int s = 0; s < AB; ++s)
+        for (int s = 0; s < AB; ++s) {
+          if (s0 + s >= KH) continue;
 #pragma unroll
           for (int ts = 0; ts < TPW; ++ts) mma_16x16x32(acc[ts], af[s], wf[ts][s0 + s]);
+        }
       }
     }
 
@@ -446,26 +450,51 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
 // cell backward (dc carried in registers) is spread over the first seven
 // waves in items of one row per lane, an equal number per SIMD, while the
 // last wave polls the step barrier.
+//
+// A wave's k-slice in chunks of four k-steps (256 bytes of a row), then what
+// is left as two and one (hidden sizes that are odd multiples of 64).
+struct BwdChunks {
+  int kw;
+  constexpr int full() const { return kw / 4; }
+  constexpr int rem() const { return kw % 4; }
+  constexpr int count() const { return full() + (rem() == 0 ? 0 : rem() == 3 ? 2 : 1); }
+  constexpr int steps(int c) const { return c < full() ? 4 : rem() != 3 ? rem() : c == full() ? 2 : 1; }
+  constexpr int start(int c) const { return c <= full() ? 4 * c : 4 * full() + 2; }
+};
+// Chunk buffers per wave, and the LDS bytes of a wave's buffers (end to end
+// where every chunk has its own).
 constexpr int bwd_chunk_buffers(int MT, int KW) {
-  const int ch = KW >= 4 ? 4 : KW, nch = KW / ch;
-  const int fit = 160 * 1024 / (8 * 16 * MT * ch * 64);  // buffer sets the LDS holds
-  return nch < fit ? nch : (fit < 2 ? fit : 2);
+  const int nch = BwdChunks{KW}.count();
+  if (8 * 16 * MT * KW * 64 <= 160 * 1024) return nch;
+  return nch < 2 ? nch : 2;
+}
+constexpr int bwd_wave_bytes(int MT, int KW) {
+  const BwdChunks ch{KW};
+  const int nb = bwd_chunk_buffers(MT, KW);
+  return 16 * MT * 64 * (nb == ch.count() ? KW : nb * ch.steps(0));
+}
+template <int N, typename F, int I = 0> __device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, F, I + 1>(static_cast<F&&>(f));
+  }
 }
 template <int MT, int NTU, int KW>
 __global__ __launch_bounds__(512, 1) void lstm_bwd_xcd(PersistBwd a, PersistSchedule ps, XcdSync y) {
   constexpr int RB = 16 * MT;                 // sequences per block
-  constexpr int CH = KW >= 4 ? 4 : KW;        // k-steps per chunk
-  constexpr int NCH = KW / CH;                // chunks per step
+  constexpr BwdChunks CK{KW};
+  constexpr int NCH = CK.count();                // chunks per step
   constexpr int NB = bwd_chunk_buffers(MT, KW);  // chunk buffers per wave
-  constexpr int CPR = CH * 4;                 // 16-byte pieces per chunk row
-  constexpr int SW = (CPR < 8 ? CPR : 8) - 1; // swizzle mask
-  constexpr int CHB = RB * CH * 64;           // bytes per chunk
-  constexpr int IPC = CHB / 1024;             // direct loads per chunk
-  static_assert(KW % CH == 0 && IPC >= 1, "chunking");
+  constexpr int CHB = RB * CK.steps(0) * 64;     // bytes per buffer
+  constexpr int WB = bwd_wave_bytes(MT, KW);
   static_assert(NB >= 1 && NB <= NCH, "chunk buffers");
+  static_assert(NB == NCH || KW % 4 == 0, "buffers used in turn: chunks of one size");
+  static_assert(8 * WB <= 160 * 1024, "LDS");
+  // element offset of chunk c in the wave's buffers
+  auto chunk_at = [](int c) constexpr { return NB == NCH ? BwdChunks{KW}.start(c) * RB * 32 : (c % NB) * (CHB / 2); };
   static_assert(MT * NTU * 4 <= 32, "cell items: at most 8 per SIMD");
   extern __shared__ __align__(16) unsigned char lds[];
-  bf16_t* buf = reinterpret_cast<bf16_t*>(lds + (threadIdx.x >> 6) * NB * CHB);
+  bf16_t* buf = reinterpret_cast<bf16_t*>(lds + (threadIdx.x >> 6) * WB);
   f32x4_t* red = reinterpret_cast<f32x4_t*>(lds);  // [8][MT][NTU][64], after the products
   __shared__ int bad_sh;
 
@@ -473,7 +502,7 @@ __global__ __launch_bounds__(512, 1) void lstm_bwd_xcd(PersistBwd a, PersistSche
   const int H = a.hidden, G4 = 4 * H, U = y.units;
   const int members = H / U;
   const int blk = xcd_block(members), us = (blockIdx.x / NX) % members;
-  const int b0 = blk * RB, j0 = us * U;
+  const int b0 = ps.first + blk * RB, j0 = us * U;
   const bf16_t* __restrict__ WhT = static_cast<const bf16_t*>(a.WhT);
   const bf16_t* __restrict__ dHa = static_cast<const bf16_t*>(a.dHa);
   const bf16_t* __restrict__ Gb = static_cast<const bf16_t*>(a.G);
@@ -570,49 +599,52 @@ __global__ __launch_bounds__(512, 1) void lstm_bwd_xcd(PersistBwd a, PersistSche
       // polled from the last wave, which has no cell work and no loads in flight
       xwait(y, local, blk, members, done, 7);
       const bf16_t* dAn = dA + (int64_t)off_next * G4 + wave * KW * 32;
-      // chunk c of this wave's k-slice into buffer bi: RB rows x CH k-steps;
-      // instruction i covers rows i*(64/CPR) .., 16-byte pieces swizzled by row
-      auto issue = [&](int c, int bi) {
+      // chunk c of this wave's k-slice into its buffer: RB rows of
+      // steps(c) k-steps; instruction i covers rows i*(64/CPR) .., 16-byte
+      // pieces swizzled by row
+      auto issue = [&](auto cc) {
+        constexpr int c = decltype(cc)::value, CPR = CK.steps(c) * 4, SW = (CPR < 8 ? CPR : 8) - 1;
 #pragma unroll
-        for (int i = 0; i < IPC; ++i) {
+        for (int i = 0; i < MT * CK.steps(c); ++i) {
           const int row = i * (64 / CPR) + lane / CPR;
           const int piece = (lane % CPR) ^ (row & SW);
-          dma16(dAn + (int64_t)min(b0 + row, nb_next - 1) * G4 + c * CH * 32 + piece * 8,
-                __builtin_amdgcn_readfirstlane(lds_address(buf + bi * (CHB / 2) + i * 512)));
+          dma16(dAn + (int64_t)min(b0 + row, nb_next - 1) * G4 + CK.start(c) * 32 + piece * 8,
+                __builtin_amdgcn_readfirstlane(lds_address(buf + chunk_at(c) + i * 512)));
         }
       };
       // the first NB chunks at once (every chunk where the buffers allow:
       // one memory latency per step rather than one per buffer round), then
       // the cell inputs; chunk c + NB goes into chunk c's buffer once c has
       // been read
-#pragma unroll
-      for (int c = 0; c < NB; ++c) issue(c, c);
+      static_for<NB>(issue);
       load_cell();
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
+      static_for<NCH>([&](auto cc) {
+        constexpr int c = decltype(cc)::value, ST = CK.steps(c), SW = (ST < 2 ? 4 : 8) - 1;
         // in flight behind chunk c at its wait: the chunks issued after it
         // (up to c + NB - 1) and, while c is one of the first NB, the cell
         // loads
-        wait_vm_n<40>(((c + NB < NCH ? c + NB : NCH) - c - 1) * IPC + (c < NB ? NL : 0));
-        const bf16_t* bb = buf + (c % NB) * (CHB / 2);
+        constexpr int last = c + NB < NCH ? c + NB : NCH;  // chunks issued so far
+        constexpr int end = CK.start(last - 1) + CK.steps(last - 1);
+        wait_vm_n<40>((end - CK.start(c) - ST) * MT + (c < NB ? NL : 0));
+        const bf16_t* bb = buf + chunk_at(c);
 #pragma unroll
-        for (int ks = 0; ks < CH; ++ks) {
+        for (int ks = 0; ks < ST; ++ks) {
           Frag<bf16_t> af[MT];
 #pragma unroll
           for (int m = 0; m < MT; ++m) {
             const int row = m * 16 + (lane & 15), piece = ks * 4 + (lane >> 4);
-            af[m] = *reinterpret_cast<const Frag<bf16_t>*>(bb + row * CH * 32 + ((piece ^ (row & SW)) << 3));
+            af[m] = *reinterpret_cast<const Frag<bf16_t>*>(bb + row * ST * 32 + ((piece ^ (row & SW)) << 3));
           }
 #pragma unroll
           for (int n = 0; n < NTU; ++n)
 #pragma unroll
-            for (int m = 0; m < MT; ++m) mma_16x16x32(acc[m][n], af[m], wb[c * CH + ks][n]);
+            for (int m = 0; m < MT; ++m) mma_16x16x32(acc[m][n], af[m], wb[CK.start(c) + ks][n]);
         }
-        if (c + NB < NCH) {
+        if constexpr (c + NB < NCH) {
           __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this buffer's reads are done
-          issue(c + NB, c % NB);
+          issue(std::integral_constant<int, c + NB>{});
         }
-      }
+      });
     } else {
       load_cell();
     }
@@ -656,10 +688,10 @@ __global__ __launch_bounds__(512, 1) void lstm_bwd_xcd(PersistBwd a, PersistSche
 
 // ------------------------------------------------------------------ launch --
 
-// Units per workgroup: the least multiple of 4 dividing H with at most
+// Units per workgroup: the least multiple of `step` dividing H with at most
 // `members` workgroups per block.
-int xcd_units(int H, int members) {
-  for (int U = 4; U <= H; U += 4)
+int xcd_units(int H, int members, int step) {
+  for (int U = step; U <= H; U += step)
     if (H % U == 0 && H / U <= members) return U;
   return 0;
 }
@@ -686,33 +718,31 @@ hipError_t coop(K kernel, int blocks, int threads, size_t lds, void** args, hipS
   return resident_launch(fn, dim3(blocks), dim3(threads), args, lds, s);
 }
 
-// Shapes covered: bf16 (the resident slices are sized for it), B <= 256,
-// hidden sizes with H % 64 == 0 and the resident weight slices within the
-// register budget.  Blocks hold RB = 16 MT sequences; BPX blocks share an
-// XCD, each served by 32 / BPX workgroups.  B > 128 takes blocks of 16, two
-// per XCD (AM_XCD_BLOCKS=1 in the environment selects blocks of 32, one per
-// XCD): per step each workgroup then reads half as many exchanged bytes
-// (16 rows instead of 32) for twice as many units, and the backward's unit
-// tiles are full (48 units = 3 x 16 instead of 24 = 16 + 8).
+// Shapes covered: bf16 (the resident slices are sized for it), hidden sizes
+// that are multiples of 64 with the resident weight slices within the
+// register budget (H <= 1024; 192 apart, which the kernels are not built
+// for), B up to MAX_ROUNDS launches.  Blocks hold 16 sequences.  Up to 128 of
+// them take one block per XCD, served by up to 32 workgroups; more take two
+// per XCD of up to 16 workgroups each where their slices fit (H <= 768): per
+// step each workgroup then reads the same exchanged bytes for twice as many
+// units.  Beyond what one launch holds, the sequences go in rounds.
+// AM_XCD_BLOCKS=1 in the environment selects blocks of 32 sequences for 128 <
+// B <= 256 (MT = 2; hidden 64, 128 and 768).
 struct XShape {
-  int MT, BPX, KS, U, NT, TPW, NTU, KW;
+  int MT, BPX, KS, U, NT, TPW, NTU, KW, rounds;
   bool ok;
 };
 
-XShape xshape(int H, int B) {
+XShape xshape_of(int H, int MT, int BPX, int U) {
   XShape x{};
-  x.ok = false;
-  if (H % 64 != 0 || B > 256 || B < 1) return x;
-  const char* e = getenv("AM_XCD_BLOCKS");
-  const bool one = e && e[0] == '1' && e[1] == 0;
-  x.MT = B > 128 && one ? 2 : 1;
-  x.BPX = B > 128 && !one ? 2 : 1;
+  x.MT = MT;
+  x.BPX = BPX;
   x.KS = H / 32;
-  x.U = xcd_units(H, 32 / x.BPX);
-  if (x.U == 0) return x;
-  x.NT = x.U / 4;
-  x.TPW = (x.MT * x.NT + 3) / 4;
-  x.NTU = (x.U + 15) / 16;
+  x.U = U;
+  if (U == 0) return x;
+  x.NT = U / 4;
+  x.TPW = (MT * x.NT + 3) / 4;
+  x.NTU = (U + 15) / 16;
   x.KW = 4 * H / 32 / 8;  // backward k-steps per wave (eight waves)
   // resident weight fragments per wave (4 VGPRs each): forward TPW x KS/2,
   // backward KW x NTU
@@ -720,11 +750,38 @@ XShape xshape(int H, int B) {
   return x;
 }
 
-}  // namespace
+XShape xshape(int H, int B) {
+  XShape x{};
+  if (H % 64 != 0 || H == 192 || B < 1) return x;
+  const char* e = getenv("AM_XCD_BLOCKS");
+  const bool one = e && e[0] == '1' && e[1] == 0;
+  if (one && B > 128 && B <= 256 && (H == 64 || H == 128 || H == 768)) {
+    x = xshape_of(H, 2, 1, xcd_units(H, 32, 4));
+    x.rounds = 1;
+    return x;
+  }
+  // whole 16-unit tiles if the width has such slices, else whole 16-byte
+  // chunks of the staged rows, else whole MFMA tiles of 4 units x 4 gates
+  for (int bpx = B > 128 ? 2 : 1; bpx > 0 && !x.ok; --bpx)
+    for (int step : {16, 8, 4}) {
+      x = xshape_of(H, 1, bpx, xcd_units(H, 32 / bpx, step));
+      if (x.ok) break;
+    }
+  x.rounds = (B + 128 * x.BPX - 1) / (128 * x.BPX);
+  if (x.rounds > XCD_MAX_ROUNDS) x.ok = false;
+  return x;
+}
 
-#define AM_FWD_CASE(MT_, KS_, TPW_, STG_)                                                \
-  if (x.MT == MT_ && x.KS == KS_ && x.TPW == TPW_ && (x.U % 8 == 0) == STG_)             \
-    return coop(lstm_fwd_xcd<MT_, KS_, TPW_, STG_>, blocks, 512, lds, args, s, used);
+// The sequences of round r, and its slot of the sync area.
+void xcd_round(const XShape& x, int r, PersistSchedule& ps, XcdSync& y) {
+  ps.first = r * 128 * x.BPX;
+  if (r > 0) {
+    y.flags += XCD_SYNC_WORDS;
+    y.xcc += XCD_SYNC_WORDS;
+  }
+}
+
+}  // namespace
 
 // AM_XCD_FENCED=1 in the environment: exchange with fences (as a block that
 // spans XCDs does) even when every block sits on one XCD.
@@ -732,6 +789,11 @@ bool fenced_forced() {
   const char* e = getenv("AM_XCD_FENCED");
   return e && e[0] == '1' && e[1] == 0;
 }
+
+#define AM_FWD_CASE(MT_, KS_, TPW_, STG_)                                                \
+  if (x.MT == MT_ && x.KS == KS_ && x.TPW == TPW_ && (x.U % 8 == 0) == STG_)             \
+    e = coop(lstm_fwd_xcd<MT_, KS_, TPW_, STG_>, blocks, 512, lds, args, s, used);       \
+  else
 
 hipError_t lstm_fwd_xcd_launch(PersistFwd a, PersistSchedule ps, XcdSync y, hipStream_t s, bool* used) {
   *used = false;
@@ -743,19 +805,33 @@ hipError_t lstm_fwd_xcd_launch(PersistFwd a, PersistSchedule ps, XcdSync y, hipS
   // h rows, partial tiles, and (U % 8 == 0) the staged rows of C, Hs and G
   const size_t lds = (size_t)16 * x.MT * x.KS * 64 + 8 * x.TPW * 64 * 16 +
                      (x.U % 8 == 0 ? (size_t)16 * x.MT * (14 * x.U + 48) : 0);
-  void* args[] = {&a, &ps, &y};
-  // instantiated shapes: H = 768 (B <= 128, B <= 256 in blocks of 16 or 32),
-  // H = 64, 128
-  AM_FWD_CASE(1, 24, 3, true) AM_FWD_CASE(2, 24, 3, true) AM_FWD_CASE(1, 24, 2, true)
-  AM_FWD_CASE(2, 2, 1, false) AM_FWD_CASE(1, 2, 1, false)
-  AM_FWD_CASE(2, 4, 1, false) AM_FWD_CASE(1, 4, 1, false)
-  AM_FWD_CASE(2, 4, 1, true) AM_FWD_CASE(1, 4, 1, true)
+  for (int r = 0; r < x.rounds; ++r) {
+    xcd_round(x, r, ps, y);
+    void* args[] = {&a, &ps, &y};
+    hipError_t e = hipSuccess;
+    // one block per XCD: 16 units up to H = 512, 32 beyond
+    AM_FWD_CASE(1, 2, 1, true) AM_FWD_CASE(1, 4, 1, true) AM_FWD_CASE(1, 8, 1, true)
+    AM_FWD_CASE(1, 10, 1, true) AM_FWD_CASE(1, 12, 1, true) AM_FWD_CASE(1, 14, 1, true)
+    AM_FWD_CASE(1, 16, 1, true) AM_FWD_CASE(1, 18, 2, true) AM_FWD_CASE(1, 20, 2, true)
+    AM_FWD_CASE(1, 22, 2, true) AM_FWD_CASE(1, 24, 2, true) AM_FWD_CASE(1, 26, 2, true)
+    AM_FWD_CASE(1, 28, 2, true) AM_FWD_CASE(1, 30, 2, true) AM_FWD_CASE(1, 32, 2, true)
+    // two: 16 units up to H = 256 (above), 32 up to 512, then 48, 40 and 44
+    AM_FWD_CASE(1, 10, 2, true) AM_FWD_CASE(1, 12, 2, true) AM_FWD_CASE(1, 14, 2, true)
+    AM_FWD_CASE(1, 16, 2, true) AM_FWD_CASE(1, 18, 3, true) AM_FWD_CASE(1, 20, 3, true)
+    AM_FWD_CASE(1, 22, 3, false) AM_FWD_CASE(1, 24, 3, true)
+    AM_FWD_CASE(2, 2, 1, false) AM_FWD_CASE(2, 4, 1, false) AM_FWD_CASE(2, 24, 3, true)
+    return hipSuccess;
+    if (e != hipSuccess || !*used) return e;
+  }
   return hipSuccess;
 }
 
 #define AM_BWD_CASE(MT_, NTU_, KW_)                                                       \
-  if (x.MT == MT_ && x.NTU == NTU_ && x.KW == KW_)                                       \
-    return coop(lstm_bwd_xcd<MT_, NTU_, KW_>, blocks, 512, lds, args, s, used);
+  if (x.MT == MT_ && x.NTU == NTU_ && x.KW == KW_) {                                     \
+    lds = 8 * (size_t)bwd_wave_bytes(MT_, KW_);                                          \
+    if (lds < red) lds = red;                                                            \
+    e = coop(lstm_bwd_xcd<MT_, NTU_, KW_>, blocks, 512, lds, args, s, used);             \
+  } else
 
 hipError_t lstm_bwd_xcd_launch(PersistBwd a, PersistSchedule ps, XcdSync y, hipStream_t s, bool* used) {
   *used = false;
@@ -765,25 +841,26 @@ hipError_t lstm_bwd_xcd_launch(PersistBwd a, PersistSchedule ps, XcdSync y, hipS
   y.fenced = fenced_forced() ? 1 : 0;
   const int blocks = NX * x.BPX * (a.hidden / x.U);
   // the waves' private chunk buffers, or the partial products if larger
-  const int ch = x.KW >= 4 ? 4 : x.KW;
-  const size_t chunks = (size_t)8 * bwd_chunk_buffers(x.MT, x.KW) * 16 * x.MT * ch * 64;
   const size_t red = (size_t)8 * x.MT * x.NTU * 64 * 16;
-  const size_t lds = chunks > red ? chunks : red;
-  void* args[] = {&a, &ps, &y};
-  AM_BWD_CASE(1, 3, 12) AM_BWD_CASE(2, 2, 12) AM_BWD_CASE(1, 2, 12)
-  AM_BWD_CASE(2, 1, 1) AM_BWD_CASE(1, 1, 1)
-  AM_BWD_CASE(2, 1, 2) AM_BWD_CASE(1, 1, 2)
+  for (int r = 0; r < x.rounds; ++r) {
+    xcd_round(x, r, ps, y);
+    void* args[] = {&a, &ps, &y};
+    hipError_t e = hipSuccess;
+    size_t lds = 0;
+    // (the same unit slices as the forward's)
+    AM_BWD_CASE(1, 1, 1) AM_BWD_CASE(1, 1, 2) AM_BWD_CASE(1, 1, 4) AM_BWD_CASE(1, 1, 5)
+    AM_BWD_CASE(1, 1, 6) AM_BWD_CASE(1, 1, 7) AM_BWD_CASE(1, 1, 8) AM_BWD_CASE(1, 2, 9)
+    AM_BWD_CASE(1, 2, 10) AM_BWD_CASE(1, 2, 11) AM_BWD_CASE(1, 2, 12) AM_BWD_CASE(1, 2, 13)
+    AM_BWD_CASE(1, 2, 14) AM_BWD_CASE(1, 2, 15) AM_BWD_CASE(1, 2, 16)
+    AM_BWD_CASE(1, 2, 5) AM_BWD_CASE(1, 2, 6) AM_BWD_CASE(1, 2, 7) AM_BWD_CASE(1, 2, 8)
+    AM_BWD_CASE(1, 3, 9) AM_BWD_CASE(1, 3, 10) AM_BWD_CASE(1, 3, 11) AM_BWD_CASE(1, 3, 12)
+    AM_BWD_CASE(2, 1, 1) AM_BWD_CASE(2, 1, 2) AM_BWD_CASE(2, 2, 12)
+    return hipSuccess;
+    if (e != hipSuccess || !*used) return e;
+  }
   return hipSuccess;
 }
 
-bool lstm_xcd_instantiated(bool forward, int hidden, int B) {
-  const XShape x = xshape(hidden, B);
-  if (!x.ok) return false;
-  if (forward)
-    return (x.KS == 24 && ((x.MT == 2 && x.TPW == 3) || (x.MT == 1 && (x.TPW == 2 || x.TPW == 3)))) ||
-           ((x.KS == 2 || x.KS == 4) && x.TPW == 1);
-  return (x.KW == 12 && (x.NTU == 2 || (x.MT == 1 && x.NTU == 3))) ||
-         ((x.KW == 1 || x.KW == 2) && x.NTU == 1);
-}
+bool lstm_xcd_instantiated(int hidden, int B) { return xshape(hidden, B).ok; }
 
 }  // namespace am

@@ -1,0 +1,58 @@
+"""GPU parity of the recurrence kernels over the hidden sizes and batch sizes
+they are built for, against the fp64 oracle: every instantiation of the
+XCD-local kernels (one and two blocks of sequences per XCD, whole and partial
+blocks, several rounds of sequences), variable lengths and carried state."""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1904_10584_amd import binding as am
+from tests.gpu_util import gpu_forward_backward, oracle_forward_backward, say
+from tests.test_gpu_model import BF16_TOL, _check, _problem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def default_paths(monkeypatch):
+    for k in ("AM_STEP_KERNELS", "AM_XCD_FENCED", "AM_RECURRENCE", "AM_XCD_BLOCKS"):
+        monkeypatch.delenv(k, raising=False)
+
+
+# (hidden, sequences): sequences 33 fill two blocks and start a third, 150 use
+# two blocks per XCD (up to hidden 768) or two rounds, 270 and 400 more rounds
+SHAPES = [(64, 33), (64, 270), (128, 150), (192, 33), (256, 33), (256, 150), (320, 33), (320, 150),
+          (384, 33), (384, 150), (448, 33), (448, 150), (512, 33), (512, 270), (576, 33), (576, 150),
+          (640, 33), (640, 150), (704, 33), (704, 150), (768, 33), (768, 270), (832, 33), (896, 33),
+          (960, 150), (1024, 33), (1024, 400)]
+
+
+@pytest.mark.parametrize("hidden,B", SHAPES)
+def test_bf16_recurrence_shapes(hidden, B):
+    dims = oracle.ModelDims(2, 40, hidden, 72)
+    T = 5
+    lengths = np.sort(np.random.default_rng(hidden + B).integers(0, T + 1, B))[::-1].astype(np.int32)
+    lengths[0] = T
+    m = am.Model(dims.layers, dims.input_dim, dims.hidden, dims.classes, am.BF16)
+    say(f"recurrence shape H={hidden} B={B} path {am.recurrence_path(m, T, B, True)}")
+    master, x, idx, prob, h0, c0 = _problem(dims, T, B, 6, 0.98, lengths, seed=23, state=True)
+    got = gpu_forward_backward(m, master, x, T, B, idx, prob, lengths, h0, c0, want_state=True)
+    ref = oracle_forward_backward(dims, master, x, T, B, idx, prob, lengths, h0, c0, bf16=True)
+    _check(got, ref, dims, BF16_TOL, state=True)
+
+
+@pytest.mark.parametrize("hidden,B", [(256, 20), (512, 48), (704, 140), (1024, 130)])
+def test_bf16_recurrence_shapes_run_repeatedly(hidden, B):
+    # many steps on warm caches, several passes on one workspace: every pass
+    # gives the first one's bits, and no step barrier runs out
+    dims = oracle.ModelDims(1, 40, hidden, 72)
+    T = 60
+    m = am.Model(dims.layers, dims.input_dim, dims.hidden, dims.classes, am.BF16)
+    say(f"recurrence repeat H={hidden} B={B}")
+    master, x, idx, prob, _, _ = _problem(dims, T, B, 6, 0.98, seed=29)
+    first = gpu_forward_backward(m, master, x, T, B, idx, prob)
+    for _ in range(3):
+        again = gpu_forward_backward(m, master, x, T, B, idx, prob)
+        for k in ("logits", "dlogits", "grads"):
+            np.testing.assert_array_equal(again[k].view(np.uint32), first[k].view(np.uint32))
