@@ -139,7 +139,9 @@ struct XcdSync {
 // left to the per-step kernels, whose products fill the chip by then.
 constexpr int XCD_SYNC_WORDS = 8192 / 4;
 constexpr int XCD_MAX_ROUNDS = 4;
-bool lstm_xcd_instantiated(int hidden, int B);
+// Whether the XCD-local kernels run a layer of this size over B sequences of T
+// steps.
+bool lstm_xcd_covers(int hidden, int B, int T);
 // Launch of a grid that the caller has checked fits on the device at once
 // (occupancy x CUs).  With AM_COOPERATIVE=1 in the environment it goes
 // through the cooperative launch (which guarantees co-residency but adds

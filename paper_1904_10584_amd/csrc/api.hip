@@ -246,7 +246,7 @@ static_assert(512 + 512 <= SYNC_STICKY_WORD, "a slot holds the flag and XCC line
 // shape instantiated, and (variable lengths) T within the schedule's 16-bit
 // lengths.
 bool xcd_shape(bool bf, int64_t H, int T, int B, bool varlen) {
-  return bf && xcd_enabled() && am::lstm_xcd_instantiated((int)H, B) &&
+  return bf && xcd_enabled() && am::lstm_xcd_covers((int)H, B, T) &&
          (!varlen || T <= 65535);
 }
 bool xcd_path(bool bf, int64_t H, const Schedule& sc) {

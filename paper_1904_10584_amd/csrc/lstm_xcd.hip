@@ -197,6 +197,7 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
   const int members = H / U;
   const int blk = xcd_block(members), us = (blockIdx.x / NX) % members;
   const int b0 = ps.first + blk * RB, j0 = us * U;
+  if (b0 >= ps.B) return;  // no sequences: no weights to load (the whole block returns)
   const int mw = g % MT;
   const int CSB = U * 4 + 16, HSB = U * 2 + 16, GSB = U * 8 + 16;  // staged row strides
   unsigned char* stH = stC + RB * CSB;
@@ -503,6 +504,7 @@ __global__ __launch_bounds__(512, 1) void lstm_bwd_xcd(PersistBwd a, PersistSche
   const int members = H / U;
   const int blk = xcd_block(members), us = (blockIdx.x / NX) % members;
   const int b0 = ps.first + blk * RB, j0 = us * U;
+  if (b0 >= ps.B) return;  // no sequences: no weights to load (the whole block returns)
   const bf16_t* __restrict__ WhT = static_cast<const bf16_t*>(a.WhT);
   const bf16_t* __restrict__ dHa = static_cast<const bf16_t*>(a.dHa);
   const bf16_t* __restrict__ Gb = static_cast<const bf16_t*>(a.G);
@@ -861,6 +863,17 @@ hipError_t lstm_bwd_xcd_launch(PersistBwd a, PersistSchedule ps, XcdSync y, hipS
   return hipSuccess;
 }
 
-bool lstm_xcd_instantiated(int hidden, int B) { return xshape(hidden, B).ok; }
+// A launch costs about as much as four steps, so a batch that needs several
+// rounds has to be long enough to pay for them (2 x 1024, 400 sequences in 4
+// rounds: 2 steps 483 us a training step against 297 one launch per step; 512
+// sequences, 20 steps: 2047 against 2303; 2 x 512, 400 in 2 rounds: 2 steps 243
+// against 220); and where one launch per step is the other choice (beyond
+// H = 768 no device-scope kernel fits) a single step is left to it (4 x 1024,
+// 4 sequences: 115 against 88 us forward).
+bool lstm_xcd_covers(int hidden, int B, int T) {
+  const XShape x = xshape(hidden, B);
+  if (!x.ok || (x.rounds > 1 && T < 4 * x.rounds)) return false;
+  return T > 1 || hidden <= 768;
+}
 
 }  // namespace am
