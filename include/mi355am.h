@@ -97,6 +97,9 @@ const char* am_last_error(void);
 /* Which kernels run one layer's recurrence (forward = 1: the forward pass;
  * 0: BPTT) for a batch of B sequences and T steps (varlen = 1 if their
  * lengths differ), as lstm_am_forward / lstm_am_backward choose them:
+ *   AM_PATH_SOLO   one launch per layer, each workgroup running 16 sequences
+ *                  through every step by itself (narrow layers; variable
+ *                  lengths need T <= 65535);
  *   AM_PATH_XCD    one persistent launch per layer whose blocks of sequences
  *                  each exchange state inside one XCD's L2 (bf16, shapes the
  *                  kernels are built for; variable lengths need T <= 65535);
@@ -106,7 +109,7 @@ const char* am_last_error(void);
  *   AM_PATH_STEP   one launch per time step.
  * A persistent grid that cannot be resident at launch falls back to the
  * next path.  -1 if the model or sizes are invalid.  Host only. */
-enum { AM_PATH_XCD = 1, AM_PATH_DEVICE = 2, AM_PATH_STEP = 3 };
+enum { AM_PATH_XCD = 1, AM_PATH_DEVICE = 2, AM_PATH_STEP = 3, AM_PATH_SOLO = 4 };
 int32_t am_recurrence_path(const am_model* m, int32_t T, int32_t B, int32_t varlen,
                            int32_t forward);
 

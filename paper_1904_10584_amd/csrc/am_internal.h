@@ -154,6 +154,12 @@ hipError_t resident_launch(const void* fn, dim3 grid, dim3 block, void** args, s
 hipError_t lstm_fwd_xcd_launch(PersistFwd a, PersistSchedule ps, XcdSync y, hipStream_t s, bool* used);
 hipError_t lstm_bwd_xcd_launch(PersistBwd a, PersistSchedule ps, XcdSync y, hipStream_t s, bool* used);
 
+// Narrow layers: one workgroup runs 16 sequences through every step, W_h in
+// its registers; no workgroup waits for another.
+bool lstm_solo_covers(int hidden, bool bf16);
+hipError_t lstm_fwd_solo_launch(PersistFwd a, PersistSchedule ps, bool bf16, hipStream_t s);
+hipError_t lstm_bwd_solo_launch(PersistBwd a, PersistSchedule ps, bool bf16, hipStream_t s);
+
 // Whether the persistent kernel covers this shape and its grid can be
 // resident at once on the current device.
 bool lstm_persistent_fits(bool forward, int hidden, int B, bool bf16, int T);

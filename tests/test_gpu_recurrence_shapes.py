@@ -9,7 +9,7 @@ import pytest
 import oracle
 from paper_1904_10584_amd import binding as am
 from tests.gpu_util import gpu_forward_backward, oracle_forward_backward, say
-from tests.test_gpu_model import BF16_TOL, _check, _problem
+from tests.test_gpu_model import BF16_TOL, F32_TOL, _check, _problem
 
 pytestmark = pytest.mark.gpu
 
@@ -40,6 +40,28 @@ def test_bf16_recurrence_shapes(hidden, B):
     got = gpu_forward_backward(m, master, x, T, B, idx, prob, lengths, h0, c0, want_state=True)
     ref = oracle_forward_backward(dims, master, x, T, B, idx, prob, lengths, h0, c0, bf16=True)
     _check(got, ref, dims, BF16_TOL, state=True)
+
+
+# one workgroup per 16 sequences: every width it is built for, a lone sequence,
+# a whole workgroup, one more; one step, fewer and more steps than the operand
+# ring has slots
+@pytest.mark.parametrize("dtype,hidden", [("bf16", h) for h in range(16, 129, 16)] +
+                         [("f32", h) for h in range(16, 97, 16)])
+@pytest.mark.parametrize("B,T,varlen", [(1, 1, False), (16, 3, True), (17, 11, True), (40, 4, False)])
+def test_narrow_layers(dtype, hidden, B, T, varlen):
+    bf16 = dtype == "bf16"
+    dims = oracle.ModelDims(2, 24, hidden, 40)
+    lengths = None
+    if varlen:
+        lengths = np.sort(np.random.default_rng(hidden + B).integers(0, T + 1, B))[::-1].astype(np.int32)
+        lengths[0] = T
+    m = am.Model(dims.layers, dims.input_dim, dims.hidden, dims.classes, am.BF16 if bf16 else am.F32)
+    assert am.recurrence_path(m, T, B, varlen) == am.PATH_SOLO
+    say(f"narrow layer {dtype} H={hidden} B={B} T={T} varlen={varlen}")
+    master, x, idx, prob, h0, c0 = _problem(dims, T, B, 6, 0.98, lengths, seed=37, state=True)
+    got = gpu_forward_backward(m, master, x, T, B, idx, prob, lengths, h0, c0, want_state=True)
+    ref = oracle_forward_backward(dims, master, x, T, B, idx, prob, lengths, h0, c0, bf16=bf16)
+    _check(got, ref, dims, BF16_TOL if bf16 else F32_TOL, state=True)
 
 
 @pytest.mark.parametrize("hidden,B", [(256, 20), (512, 48), (704, 140), (1024, 130)])
