@@ -260,14 +260,18 @@ bool xcd_path(bool bf, int64_t H, const Schedule& sc) {
 }
 
 // Narrow layers run one workgroup per 16 sequences, unless the environment
-// asks for the XCD-local or the device-scope kernels (tests).
-bool solo_shape(bool bf, int64_t H, int T, bool varlen) {
+// asks for the XCD-local or the device-scope kernels (tests).  At 128 cells a
+// step's products in one compute unit outlast the exchange between several (3
+// x 128, 5 chunks of 78 frames, step: 862 us against 798), so the XCD-local
+// kernels go first there.
+bool solo_shape(bool bf, int64_t H, int T, int B, bool varlen) {
   auto set = [](const char* name) {
     const char* v = getenv(name);
     return v && v[0] && !(v[0] == '0' && v[1] == 0);
   };
   return persistent_enabled() && !set("AM_RECURRENCE") && !set("AM_XCD_FENCED") &&
-         !set("AM_XCD_BLOCKS") && am::lstm_solo_covers((int)H, bf) && (!varlen || T <= 65535);
+         !set("AM_XCD_BLOCKS") && am::lstm_solo_covers((int)H, bf) && (!varlen || T <= 65535) &&
+         !(H == 128 && xcd_shape(bf, H, T, B, varlen));
 }
 // AM_DEBUG=1 in the environment: entry points that consume indices held in
 // device buffers synchronise and check them.
@@ -394,7 +398,7 @@ am_status forward_recurrence(const FwdLayer& f, const Schedule& sc, bool bf, int
     const double flops = 2.0 * sc.N * G * H;
     const double bytes = (double)sc.N * (G * e * 2 + H * (2 * e + 4)) + (double)G * H * e;
     bool used = false;
-    if (solo_shape(bf, H, T, ps.varlen != 0)) {
+    if (solo_shape(bf, H, T, B, ps.varlen != 0)) {
       Timed tm(AM_K_LSTM_FWD, s, flops, bytes);
       return hip_check(am::lstm_fwd_solo_launch(pa, ps, bf, s), "lstm forward layer (solo)");
     }
@@ -638,7 +642,7 @@ int32_t am_recurrence_path(const am_model* m, int32_t T, int32_t B, int32_t varl
   if (check_model(m) != AM_OK || T < 0 || B < 1) return -1;
   const bool bf = m->dtype == AM_BF16, fw = forward != 0;
   if (!persistent_enabled()) return AM_PATH_STEP;
-  if (solo_shape(bf, m->hidden, T, varlen != 0)) return AM_PATH_SOLO;
+  if (solo_shape(bf, m->hidden, T, B, varlen != 0)) return AM_PATH_SOLO;
   if (xcd_shape(bf, m->hidden, T, B, varlen != 0)) return AM_PATH_XCD;
   if (device_persistent_enabled() && am::lstm_persistent_fits(fw, m->hidden, B, bf, T))
     return AM_PATH_DEVICE;
@@ -1129,7 +1133,7 @@ am_status lstm_am_backward(const am_model* m, const void* params, const void* x,
   // the XCD-local recurrences read W_h^T: every layer's, transposed up front
   // in one launch (falls back to one transpose per layer below)
   bool wht_ready = false;
-  if (sc.N > 0 && xcd_path(bf, H, sc) && !solo_shape(bf, H, T, is_varlen(sc))) {
+  if (sc.N > 0 && xcd_path(bf, H, sc) && !solo_shape(bf, H, T, B, is_varlen(sc))) {
     Timed tm(AM_K_MISC, s, 0.0, 2.0 * L * G * H * e);
     wht_ready = true;
     for (int l0 = 0; l0 < L && wht_ready; l0 += am::TransposeBatch::MAX) {
@@ -1167,7 +1171,7 @@ am_status lstm_am_backward(const am_model* m, const void* params, const void* x,
       const am::PersistSchedule ps = persist_schedule(sc);
       const double flops = 2.0 * (sc.N - sc.counts[0]) * G * H;
       const double bytes = (double)sc.N * (G * e * 2 + H * (e + 8)) + (double)G * H * e;
-      if (solo_shape(bf, H, T, ps.varlen != 0)) {
+      if (solo_shape(bf, H, T, B, ps.varlen != 0)) {
         Timed tm(AM_K_LSTM_BWD, s, flops, bytes);
         used = true;
         AM_TRY(hip_check(am::lstm_bwd_solo_launch(pa, ps, bf, s), "lstm backward layer (solo)"));

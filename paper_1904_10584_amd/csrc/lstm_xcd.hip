@@ -513,13 +513,16 @@ __global__ __launch_bounds__(512, 1) void lstm_bwd_xcd(PersistBwd a, PersistSche
   // resident W_h^T fragments (8 consecutive k of one unit: one 16-byte load
   // of the transposed W_h): k-step wave KW + s, unit tile n, lane column
   // c -> unit j0 + 16n + min(c, vc_n - 1) (vc_n = valid columns of tile n)
+  // (H = 192: 24 k-steps, four each in the first six waves)
+  const int wv = __builtin_amdgcn_readfirstlane(wave);  // (scalar: wave-uniform indices and branches)
+  const bool has_k = wv * KW * 32 < G4;
   Frag<bf16_t> wb[KW][NTU];
 #pragma unroll
   for (int n = 0; n < NTU; ++n) {
     const int unit = j0 + 16 * n + min(lane & 15, min(16, U - 16 * n) - 1);
 #pragma unroll
     for (int s = 0; s < KW; ++s)
-      wb[s][n] = frag_load<bf16_t>(WhT + (int64_t)unit * G4 + (wave * KW + s) * 32 + (lane >> 4) * 8);
+      wb[s][n] = frag_load<bf16_t>(WhT + (int64_t)unit * G4 + (has_k ? (wave * KW + s) * 32 : 0) + (lane >> 4) * 8);
   }
   const bool local = check_local(y, blk, us, members, &bad_sh);
 
@@ -532,7 +535,6 @@ __global__ __launch_bounds__(512, 1) void lstm_bwd_xcd(PersistBwd a, PersistSche
   // rest, evenly (12 items: 2, 2, 2, 2 and 2, 1, 1).
   constexpr int NI = MT * NTU * 4, IPS = (NI + 6) / 7;
   constexpr int FIRST = NI < 4 * IPS ? NI : 4 * IPS, REST = NI - FIRST;
-  const int wv = __builtin_amdgcn_readfirstlane(wave);  // (scalar: the item indices are wave-uniform)
   int i_lo, i_hi;
   if (wv < 4) {
     i_lo = min(NI, wv * IPS);
@@ -600,6 +602,9 @@ __global__ __launch_bounds__(512, 1) void lstm_bwd_xcd(PersistBwd a, PersistSche
     if (b0 < nb_next) {
       // polled from the last wave, which has no cell work and no loads in flight
       xwait(y, local, blk, members, done, 7);
+      if (!has_k) {
+        load_cell();
+      } else {
       const bf16_t* dAn = dA + (int64_t)off_next * G4 + wave * KW * 32;
       // chunk c of this wave's k-slice into its buffer: RB rows of
       // steps(c) k-steps; instruction i covers rows i*(64/CPR) .., 16-byte
@@ -647,6 +652,7 @@ __global__ __launch_bounds__(512, 1) void lstm_bwd_xcd(PersistBwd a, PersistSche
           issue(std::integral_constant<int, c + NB>{});
         }
       });
+      }
     } else {
       load_cell();
     }
@@ -722,8 +728,7 @@ hipError_t coop(K kernel, int blocks, int threads, size_t lds, void** args, hipS
 
 // Shapes covered: bf16 (the resident slices are sized for it), hidden sizes
 // that are multiples of 64 with the resident weight slices within the
-// register budget (H <= 1024; 192 apart, which the kernels are not built
-// for), B up to MAX_ROUNDS launches.  Blocks hold 16 sequences.  Up to 128 of
+// register budget (H <= 1024), B up to XCD_MAX_ROUNDS launches.  Blocks hold 16 sequences.  Up to 128 of
 // them take one block per XCD, served by up to 32 workgroups; more take two
 // per XCD of up to 16 workgroups each where their slices fit (H <= 768): per
 // step each workgroup then reads the same exchanged bytes for twice as many
@@ -745,7 +750,7 @@ XShape xshape_of(int H, int MT, int BPX, int U) {
   x.NT = U / 4;
   x.TPW = (MT * x.NT + 3) / 4;
   x.NTU = (U + 15) / 16;
-  x.KW = 4 * H / 32 / 8;  // backward k-steps per wave (eight waves)
+  x.KW = H == 192 ? 4 : 4 * H / 32 / 8;  // backward k-steps per wave (eight waves; 192: six)
   // resident weight fragments per wave (4 VGPRs each): forward TPW x KS/2,
   // backward KW x NTU
   x.ok = x.TPW * x.KS / 2 <= 36 && x.KW * x.NTU <= 36 && x.TPW <= 3 && x.NTU <= 3;
@@ -754,7 +759,7 @@ XShape xshape_of(int H, int MT, int BPX, int U) {
 
 XShape xshape(int H, int B) {
   XShape x{};
-  if (H % 64 != 0 || H == 192 || B < 1) return x;
+  if (H % 64 != 0 || B < 1) return x;
   const char* e = getenv("AM_XCD_BLOCKS");
   const bool one = e && e[0] == '1' && e[1] == 0;
   if (one && B > 128 && B <= 256 && (H == 64 || H == 128 || H == 768)) {
@@ -812,7 +817,8 @@ hipError_t lstm_fwd_xcd_launch(PersistFwd a, PersistSchedule ps, XcdSync y, hipS
     void* args[] = {&a, &ps, &y};
     hipError_t e = hipSuccess;
     // one block per XCD: 16 units up to H = 512, 32 beyond
-    AM_FWD_CASE(1, 2, 1, true) AM_FWD_CASE(1, 4, 1, true) AM_FWD_CASE(1, 8, 1, true)
+    AM_FWD_CASE(1, 2, 1, true) AM_FWD_CASE(1, 4, 1, true) AM_FWD_CASE(1, 6, 1, true)
+    AM_FWD_CASE(1, 8, 1, true)
     AM_FWD_CASE(1, 10, 1, true) AM_FWD_CASE(1, 12, 1, true) AM_FWD_CASE(1, 14, 1, true)
     AM_FWD_CASE(1, 16, 1, true) AM_FWD_CASE(1, 18, 2, true) AM_FWD_CASE(1, 20, 2, true)
     AM_FWD_CASE(1, 22, 2, true) AM_FWD_CASE(1, 24, 2, true) AM_FWD_CASE(1, 26, 2, true)

@@ -22,7 +22,7 @@ def default_paths(monkeypatch):
 
 # (hidden, sequences): sequences 33 fill two blocks and start a third, 150 use
 # two blocks per XCD (up to hidden 768) or two rounds, 270 and 400 more rounds
-SHAPES = [(64, 33), (64, 270), (128, 150), (192, 33), (256, 33), (256, 150), (320, 33), (320, 150),
+SHAPES = [(64, 33), (64, 270), (128, 150), (128, 1000), (192, 33), (192, 150), (256, 33), (256, 150), (320, 33), (320, 150),
           (384, 33), (384, 150), (448, 33), (448, 150), (512, 33), (512, 270), (576, 33), (576, 150),
           (640, 33), (640, 150), (704, 33), (704, 150), (768, 33), (768, 270), (832, 33), (896, 33),
           (960, 150), (1024, 33), (1024, 400)]
@@ -56,7 +56,8 @@ def test_narrow_layers(dtype, hidden, B, T, varlen):
         lengths = np.sort(np.random.default_rng(hidden + B).integers(0, T + 1, B))[::-1].astype(np.int32)
         lengths[0] = T
     m = am.Model(dims.layers, dims.input_dim, dims.hidden, dims.classes, am.BF16 if bf16 else am.F32)
-    assert am.recurrence_path(m, T, B, varlen) == am.PATH_SOLO
+    if hidden < 128:
+        assert am.recurrence_path(m, T, B, varlen) == am.PATH_SOLO
     say(f"narrow layer {dtype} H={hidden} B={B} T={T} varlen={varlen}")
     master, x, idx, prob, h0, c0 = _problem(dims, T, B, 6, 0.98, lengths, seed=37, state=True)
     got = gpu_forward_backward(m, master, x, T, B, idx, prob, lengths, h0, c0, want_state=True)
