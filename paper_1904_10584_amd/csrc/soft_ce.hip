@@ -220,19 +220,46 @@ __global__ __launch_bounds__(256) void sum_partials(const float* __restrict__ pa
   if (threadIdx.x == 0) out[0] = red[0];
 }
 
-// 1 / (number of rows with a nonzero mask), 0 if there are none.
-__global__ __launch_bounds__(256) void mask_scale(const uint8_t* __restrict__ mask, int64_t n,
-                                                  float* __restrict__ out) {
-  __shared__ int64_t red[256];
+// 1 / (number of rows with a nonzero mask), 0 if there are none.  One
+// workgroup: 16 mask bytes a load, four loads in flight a thread (a byte at a
+// time, 64 loads one after another, took 23 us for 16384 rows; now 4.7).
+__global__ __launch_bounds__(1024) void mask_scale(const uint8_t* __restrict__ mask, int64_t n,
+                                                   float* __restrict__ out) {
+  __shared__ int64_t red[16];
+  // bytes before the first 16-byte boundary, whole chunks, the rest
+  const int64_t head0 = (int64_t)(-reinterpret_cast<uintptr_t>(mask) & 15), head = head0 < n ? head0 : n;
+  const int64_t chunks = (n - head) / 16;
+  const uint4* v = reinterpret_cast<const uint4*>(mask + head);
+  auto nonzero = [](uint32_t w) {  // bytes of w that are not zero
+    w |= w >> 4;
+    w |= w >> 2;
+    w |= w >> 1;
+    return __popc(w & 0x01010101u);
+  };
   int64_t cnt = 0;
-  for (int64_t i = threadIdx.x; i < n; i += 256) cnt += mask[i] != 0;
-  red[threadIdx.x] = cnt;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
+  for (int64_t i = threadIdx.x; i < chunks; i += 4 * 1024) {
+    uint4 q[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t j = i + k * 1024;
+      q[k] = v[j < chunks ? j : i];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (i + k * 1024 < chunks)
+        cnt += (nonzero(q[k].x) + nonzero(q[k].y)) + (nonzero(q[k].z) + nonzero(q[k].w));
   }
-  if (threadIdx.x == 0) out[0] = red[0] > 0 ? 1.0f / (float)red[0] : 0.f;
+  if (threadIdx.x < 16 && (int64_t)threadIdx.x < head) cnt += mask[threadIdx.x] != 0;
+  for (int64_t i = head + chunks * 16 + threadIdx.x; i < n; i += 1024) cnt += mask[i] != 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = cnt;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t all = 0;
+    for (int w = 0; w < 16; ++w) all += red[w];
+    out[0] = all > 0 ? 1.0f / (float)all : 0.f;
+  }
 }
 
 template <int NCH, typename DT>
@@ -266,7 +293,7 @@ hipError_t soft_ce(const SoftCeArgs& a, hipStream_t s) {
   float sh = 1.f;
   if (a.reduction == 0) {  // mean over valid rows
     if (a.mask) {
-      hipLaunchKernelGGL(mask_scale, dim3(1), dim3(256), 0, s, a.mask, a.N, a.ws_scale);
+      hipLaunchKernelGGL(mask_scale, dim3(1), dim3(1024), 0, s, a.mask, a.N, a.ws_scale);
       sd = a.ws_scale;
     } else {
       sh = a.N > 0 ? 1.0f / (float)a.N : 0.f;
