@@ -237,15 +237,17 @@ __device__ __forceinline__ int64_t lower_bound_wave(const uint32_t* w, int64_t c
   return lo + __popcll(__ballot(p < hi && w[p] < key));
 }
 
-template <bool ACC>
+// V4: dense is 16-byte aligned and moves as float4 (4-byte accesses: 19.2 us
+// for 24.1 M elements at a 1 % send rate, now 17.5).
+template <bool ACC, bool V4>
 __global__ __launch_bounds__(TPB) void gtc_decode_tiles(const uint32_t* __restrict__ words,
                                                         const int64_t* __restrict__ count,
                                                         int64_t capacity, float tau, int64_t n,
                                                         float* __restrict__ dense) {
-  __shared__ float tile[TILE];
+  __shared__ __align__(16) float tile[TILE];
   __shared__ int64_t range[2];
   const int64_t base = (int64_t)blockIdx.x * TILE;
-  const int64_t len = n - base < TILE ? n - base : TILE;
+  const int len = (int)(n - base < TILE ? n - base : TILE);
   if (threadIdx.x < 128) {  // wave 0: the tile's first word, wave 1: the next tile's
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     int64_t cnt = *count;
@@ -254,8 +256,16 @@ __global__ __launch_bounds__(TPB) void gtc_decode_tiles(const uint32_t* __restri
     const int64_t r = lower_bound_wave(words, cnt, (uint32_t)(end << 1), lane);
     if (lane == 0) range[wv] = r;
   }
-  for (int i = threadIdx.x; i < TILE; i += TPB)
-    tile[i] = (ACC && i < len) ? dense[base + i] : 0.f;
+  const int whole = V4 ? len & ~3 : 0;  // elements moved four at a time
+  for (int i = threadIdx.x * 4; i < TILE; i += TPB * 4) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (ACC && i < whole) v = *reinterpret_cast<const float4*>(dense + base + i);
+    *reinterpret_cast<float4*>(tile + i) = v;
+  }
+  if (ACC && whole < len) {
+    __syncthreads();
+    for (int i = whole + threadIdx.x; i < len; i += TPB) tile[i] = dense[base + i];
+  }
   __syncthreads();
   const int64_t lo = range[0], hi = range[1];
   for (int64_t w = lo + threadIdx.x; w < hi; w += TPB) {
@@ -266,9 +276,10 @@ __global__ __launch_bounds__(TPB) void gtc_decode_tiles(const uint32_t* __restri
     if (ACC) tile[i] = tile[i] + v; else tile[i] = v;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < len; i += TPB) dense[base + i] = tile[i];
+  for (int i = threadIdx.x * 4; i < whole; i += TPB * 4)
+    *reinterpret_cast<float4*>(dense + base + i) = *reinterpret_cast<const float4*>(tile + i);
+  for (int i = whole + threadIdx.x; i < len; i += TPB) dense[base + i] = tile[i];
 }
-
 
 // Decode of one stream fused with the SGD step, for a learning rate that is
 // -0.0, negative, infinite or NaN (then w - lr * 0.0 may differ from w, so
@@ -353,7 +364,11 @@ __global__ __launch_bounds__(TPB) void gtc_multi_bounds(const uint32_t* __restri
       (int32_t)lower_bound_words(words + (int64_t)s * capacity, cnt, (uint32_t)(first << 1));
 }
 
-template <bool ACC>
+// A tile's words of every stream: the streams' ranges are fetched by a lane
+// each, then a wave takes every fourth stream, the first words of four of them
+// in flight at once (walking the streams one after another, two dependent
+// loads each, took 32 us for 8 streams at 1 %; now 18).
+template <bool ACC, bool V4>
 __global__ __launch_bounds__(TPB) void gtc_multi_tiles(const uint32_t* __restrict__ words,
                                                        int64_t capacity,
                                                        const int64_t* __restrict__ counts,
@@ -361,34 +376,79 @@ __global__ __launch_bounds__(TPB) void gtc_multi_tiles(const uint32_t* __restric
                                                        const int32_t* __restrict__ start,
                                                        int64_t ntiles, float tau, int64_t n,
                                                        float* __restrict__ dense) {
-  __shared__ int acc[TILE];
+  __shared__ __align__(16) int acc[TILE];
+  __shared__ int2 range[64];
   const int64_t t = blockIdx.x, base = t * TILE;
   const int len = (int)(n - base < TILE ? n - base : TILE);
-  for (int i = threadIdx.x; i < TILE; i += TPB) acc[i] = 0;
-  __syncthreads();
-  for (int s = 0; s < streams; ++s) {
-    int64_t cnt = counts[s];
-    cnt = cnt < 0 ? 0 : (cnt > capacity ? capacity : cnt);
-    const int32_t* st = start + (int64_t)s * (ntiles + 1);
-    int64_t lo = st[t], hi = st[t + 1];
-    lo = lo < 0 ? 0 : (lo > cnt ? cnt : lo);
-    hi = hi < lo ? lo : (hi > cnt ? cnt : hi);
-    const uint32_t* w = words + (int64_t)s * capacity;
-    for (int64_t p = lo + threadIdx.x; p < hi; p += TPB) {
-      const uint32_t word = w[p];
-      const int i = (int)((word >> 1) - (uint32_t)base);
-      if ((unsigned)i >= (unsigned)len) continue;  // only for malformed streams
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = threadIdx.x * 4; i < TILE; i += TPB * 4) *reinterpret_cast<int4*>(acc + i) = make_int4(0, 0, 0, 0);
+  auto add = [&](uint32_t word) {
+    const int i = (int)((word >> 1) - (uint32_t)base);
+    if ((unsigned)i < (unsigned)len)  // (otherwise only for malformed streams)
       atomicAdd(&acc[i], (word & 1u) ? (1 << 16) - 1 : (1 << 16) + 1);
+  };
+  for (int s0 = 0; s0 < streams; s0 += 64) {
+    const int ns = streams - s0 < 64 ? streams - s0 : 64;
+    if ((int)threadIdx.x < ns) {
+      const int s = s0 + threadIdx.x;
+      int64_t cnt = counts[s];
+      const int32_t* st = start + (int64_t)s * (ntiles + 1);
+      int64_t lo = st[t], hi = st[t + 1];
+      cnt = cnt < 0 ? 0 : (cnt > capacity ? capacity : cnt);
+      lo = lo < 0 ? 0 : (lo > cnt ? cnt : lo);
+      hi = hi < lo ? lo : (hi > cnt ? cnt : hi);
+      range[threadIdx.x] = make_int2((int)lo, (int)hi);
+    }
+    __syncthreads();
+    for (int q = wave; q < ns; q += 16) {
+      uint32_t first[4];
+      int2 r[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int s = q + 4 * j;
+        r[j] = s < ns ? range[s] : make_int2(0, 0);
+        const bool has = r[j].x + lane < r[j].y;
+        // (an unconditional load, of a word or of any valid address: behind a
+        // branch it would be waited for before the next stream's)
+        first[j] = *(has ? words + (int64_t)(s0 + s) * capacity + r[j].x + lane
+                         : reinterpret_cast<const uint32_t*>(start));
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (r[j].x + lane < r[j].y) add(first[j]);
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t* w = words + (int64_t)(s0 + q + 4 * j) * capacity;
+        for (int p = r[j].x + 64 + lane; p < r[j].y; p += 64) add(w[p]);
+      }
+    }
+    __syncthreads();  // (the ranges are replaced; the last time: the sums are complete)
+  }
+  const double tau64 = (double)tau;
+  auto value = [&](int v, bool& hit) {
+    const int hits = (v + 32768) >> 16;
+    hit = hits > 0;
+    return (float)(tau64 * (double)(v - (hits << 16)));
+  };
+  if (V4) {  // (dense 16-byte aligned)
+    for (int i = threadIdx.x * 4; i + 3 < len; i += TPB * 4) {
+      const int4 v = *reinterpret_cast<const int4*>(acc + i);
+      float4* d = reinterpret_cast<float4*>(dense + base + i);
+      bool h[4];
+      const float q0 = value(v.x, h[0]), q1 = value(v.y, h[1]), q2 = value(v.z, h[2]), q3 = value(v.w, h[3]);
+      if (ACC) {
+        if (!(h[0] || h[1] || h[2] || h[3])) continue;
+        const float4 o = *d;
+        *d = make_float4(h[0] ? o.x + q0 : o.x, h[1] ? o.y + q1 : o.y, h[2] ? o.z + q2 : o.z,
+                         h[3] ? o.w + q3 : o.w);
+      } else {
+        *d = make_float4(h[0] ? q0 : 0.f, h[1] ? q1 : 0.f, h[2] ? q2 : 0.f, h[3] ? q3 : 0.f);
+      }
     }
   }
-  __syncthreads();
-  const double tau64 = (double)tau;
-  for (int i = threadIdx.x; i < len; i += TPB) {
-    const int v = acc[i];
-    const int hits = (v + 32768) >> 16;
-    const int k = v - (hits << 16);
-    if (hits > 0) {
-      const float q = (float)(tau64 * (double)k);
+  for (int i = (V4 ? len & ~3 : 0) + threadIdx.x; i < len; i += TPB) {
+    bool hit;
+    const float q = value(acc[i], hit);
+    if (hit) {
       dense[base + i] = ACC ? dense[base + i] + q : q;
     } else if (!ACC) {
       dense[base + i] = 0.f;
@@ -427,12 +487,13 @@ hipError_t gtc_decode(const uint32_t* words, const int64_t* count, int64_t capac
                       int64_t n, float* dense, bool accumulate, hipStream_t s) {
   const int64_t ntiles = gtc_tiles(n);
   if (ntiles == 0) return hipSuccess;
-  if (accumulate)
-    hipLaunchKernelGGL(gtc_decode_tiles<true>, dim3((unsigned)ntiles), dim3(TPB), 0, s, words,
-                       count, capacity, tau, n, dense);
-  else
-    hipLaunchKernelGGL(gtc_decode_tiles<false>, dim3((unsigned)ntiles), dim3(TPB), 0, s, words,
-                       count, capacity, tau, n, dense);
+  const bool v4 = (reinterpret_cast<uintptr_t>(dense) & 15) == 0;
+  auto tiles = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)ntiles), dim3(TPB), 0, s, words, count, capacity, tau, n,
+                       dense);
+  };
+  if (accumulate) tiles(v4 ? gtc_decode_tiles<true, true> : gtc_decode_tiles<true, false>);
+  else tiles(v4 ? gtc_decode_tiles<false, true> : gtc_decode_tiles<false, false>);
   return hipGetLastError();
 }
 
@@ -449,12 +510,13 @@ hipError_t gtc_decode_multi(int streams, const uint32_t* words, int64_t capacity
   const unsigned bx = (unsigned)((ntiles + 1 + TPB - 1) / TPB);
   hipLaunchKernelGGL(gtc_multi_bounds, dim3(bx, (unsigned)streams), dim3(TPB), 0, s, words,
                      capacity, counts, ntiles, n, ws_start);
-  if (accumulate)
-    hipLaunchKernelGGL(gtc_multi_tiles<true>, dim3((unsigned)ntiles), dim3(TPB), 0, s, words,
-                       capacity, counts, streams, ws_start, ntiles, tau, n, dense);
-  else
-    hipLaunchKernelGGL(gtc_multi_tiles<false>, dim3((unsigned)ntiles), dim3(TPB), 0, s, words,
-                       capacity, counts, streams, ws_start, ntiles, tau, n, dense);
+  const bool v4 = (reinterpret_cast<uintptr_t>(dense) & 15) == 0;
+  auto tiles = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)ntiles), dim3(TPB), 0, s, words, capacity, counts,
+                       streams, ws_start, ntiles, tau, n, dense);
+  };
+  if (accumulate) tiles(v4 ? gtc_multi_tiles<true, true> : gtc_multi_tiles<true, false>);
+  else tiles(v4 ? gtc_multi_tiles<false, true> : gtc_multi_tiles<false, false>);
   return hipGetLastError();
 }
 
