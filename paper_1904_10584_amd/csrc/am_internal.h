@@ -154,6 +154,27 @@ hipError_t resident_launch(const void* fn, dim3 grid, dim3 block, void** args, s
 hipError_t lstm_fwd_xcd_launch(PersistFwd a, PersistSchedule ps, XcdSync y, hipStream_t s, bool* used);
 hipError_t lstm_bwd_xcd_launch(PersistBwd a, PersistSchedule ps, XcdSync y, hipStream_t s, bool* used);
 
+// Every layer's forward recurrence in one launch, the layers one behind the
+// other in time (few sequences; see lstm_pipe.hip).  P holds the first layer's
+// input projections.
+struct PipeLayer {
+  const void* Wh;     // [4H][H]
+  const void* WxN;    // [4H][H] input weights and bias of the layer above, or null
+  const void* bN;     // [4H]
+  const void* h0;     // [B][H] or null (zero)
+  const float* c0;    // [B][H]
+  void* H; void* Hs; float* C; void* G;  // as PersistFwd's
+};
+struct PipeFwd {
+  static constexpr int MAX = 8;
+  PipeLayer l[MAX];
+  const void* P;
+  unsigned* pflags;   // set by the launcher (in the sync slot)
+  int layers, blocks, hidden;
+};
+bool lstm_pipe_covers(int hidden, int B, int layers);
+hipError_t lstm_fwd_pipe_launch(PipeFwd a, PersistSchedule ps, XcdSync y, hipStream_t s, bool* used);
+
 // Narrow layers: one workgroup runs 16 sequences through every step, W_h in
 // its registers; no workgroup waits for another.
 bool lstm_solo_covers(int hidden, bool bf16);

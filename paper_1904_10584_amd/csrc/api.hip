@@ -240,7 +240,9 @@ am::XcdSync xcd_sync(void* slot, int* err) {
   y.fenced = 0;
   return y;
 }
-static_assert(512 + 512 <= SYNC_STICKY_WORD, "a slot holds the flag and XCC lines below the time-out word");
+static_assert(1024 + 512 <= SYNC_STICKY_WORD,
+              "a slot holds the flag and XCC lines, and the second flag lines of a launch of all layers, "
+              "below the time-out word");
 
 bool is_varlen(const Schedule& sc) {
   for (int b = 0; b < sc.B; ++b)
@@ -273,6 +275,16 @@ bool solo_shape(bool bf, int64_t H, int T, int B, bool varlen) {
          !set("AM_XCD_BLOCKS") && am::lstm_solo_covers((int)H, bf) && (!varlen || T <= 65535) &&
          !(H == 128 && xcd_shape(bf, H, T, B, varlen));
 }
+// Whether the forward pass runs every layer in one launch: where the XCD-local
+// kernels would run them one after another (and no environment variable asks
+// for one path) and the layers' blocks of sequences have room side by side.
+bool pipe_path(bool bf, int64_t H, int64_t L, const Schedule& sc) {
+  const char* r = getenv("AM_RECURRENCE");
+  const char* o = getenv("AM_XCD_BLOCKS");
+  return !(r && r[0]) && !(o && o[0] == '1') && xcd_path(bf, H, sc) &&
+         !solo_shape(bf, H, sc.T, sc.B, is_varlen(sc)) && am::lstm_pipe_covers((int)H, sc.B, (int)L);
+}
+
 // AM_DEBUG=1 in the environment: entry points that consume indices held in
 // device buffers synchronise and check them.
 bool debug_checks() {
@@ -1039,13 +1051,43 @@ am_status lstm_am_forward(const am_model* m, const void* params, const void* x,
                                     c0 ? 0 : L * B * H, s), "sync and c0 clear"));
   }
 
-  for (int l = 0; l < L; ++l) {
+  // few sequences: every layer in one launch behind the first projection
+  const bool pipe = sc.N > 0 && pipe_path(bf, H, L, sc);
+  bool piped = false;
+  for (int l = 0; l < L && !piped; ++l) {
     const int64_t D = l == 0 ? m->input_dim : H;
     const void* X = l == 0 ? x : at<void>(ws, w.h[l - 1]);
     void* P = at<void>(ws, w.p_da);
     AM_TRY(run_gemm(AM_K_GEMM_FWD,
                     mk_gemm(X, D, true, P8 + po.wx[l] * e, D, true, P, G, false, P8 + po.b[l] * e,
                             (int)sc.N, (int)G, (int)D, bf), s));
+    if (pipe && l == 0) {
+      am::PipeFwd pf{};
+      for (int k = 0; k < L; ++k) {
+        am::PipeLayer& q = pf.l[k];
+        q.Wh = P8 + po.wh[k] * e;
+        q.WxN = k + 1 < L ? P8 + po.wx[k + 1] * e : nullptr;
+        q.bN = k + 1 < L ? P8 + po.b[k + 1] * e : nullptr;
+        q.h0 = h0 ? at<char>(ws, w.h0) + (int64_t)k * B * H * e : nullptr;
+        q.c0 = at<float>(ws, w.c0) + (int64_t)k * B * H;
+        q.H = at<void>(ws, w.h[k]);
+        q.Hs = at<void>(ws, w.hs[k]);
+        q.C = at<float>(ws, w.c[k]);
+        q.G = at<void>(ws, w.g[k]);
+      }
+      pf.P = P;
+      pf.layers = (int)L;
+      pf.hidden = (int)H;
+      void* area = at<void>(ws, w.sync);
+      const double nl = (double)sc.N * L;
+      Timed tm(AM_K_LSTM_FWD, s, 2.0 * nl * G * H + 2.0 * (nl - sc.N) * G * H,
+               nl * (G * e * 2 + H * (2 * e + 4)) + 2.0 * L * G * H * e);
+      AM_TRY(hip_check(am::lstm_fwd_pipe_launch(pf, persist_schedule(sc),
+                                                xcd_sync(sync_slot(area, 0, B), sync_err(area)), s, &piped),
+                       "lstm forward, all layers"));
+      if (piped) break;
+      tm.cancel();
+    }
     FwdLayer f;
     f.P = at<void>(ws, w.p_da);
     f.Wh = P8 + po.wh[l] * e;

@@ -79,3 +79,50 @@ def test_bf16_recurrence_shapes_run_repeatedly(hidden, B):
         again = gpu_forward_backward(m, master, x, T, B, idx, prob)
         for k in ("logits", "dlogits", "grads"):
             np.testing.assert_array_equal(again[k].view(np.uint32), first[k].view(np.uint32))
+
+
+# every layer in one launch: each instantiation, an XCD or half of one per
+# (layer, block), up to every slot taken; more blocks than slots (the last) go
+# layer by layer
+@pytest.mark.parametrize("layers,hidden,B,T", [
+    (2, 128, 20, 9), (8, 128, 32, 4), (3, 192, 33, 5), (4, 256, 17, 6), (2, 256, 128, 5), (2, 320, 16, 7),
+    (5, 320, 48, 4), (3, 384, 16, 5), (3, 384, 70, 5), (2, 448, 60, 4), (3, 448, 80, 4), (4, 512, 32, 5),
+    (3, 512, 48, 11), (2, 576, 16, 5), (3, 640, 20, 5), (4, 704, 32, 4), (5, 768, 12, 9), (8, 768, 1, 3),
+    (2, 768, 3, 1), (5, 512, 64, 3)])
+@pytest.mark.parametrize("varlen", [False, True])
+def test_layers_in_one_launch(layers, hidden, B, T, varlen):
+    dims = oracle.ModelDims(layers, 40, hidden, 72)
+    lengths = None
+    if varlen:
+        lengths = np.sort(np.random.default_rng(hidden + B).integers(0, T + 1, B))[::-1].astype(np.int32)
+        lengths[0] = T
+    m = am.Model(dims.layers, dims.input_dim, dims.hidden, dims.classes, am.BF16)
+    say(f"layers in one launch L={layers} H={hidden} B={B} T={T} varlen={varlen}")
+    master, x, idx, prob, h0, c0 = _problem(dims, T, B, 6, 0.98, lengths, seed=43, state=varlen)
+    got = gpu_forward_backward(m, master, x, T, B, idx, prob, lengths, h0, c0, want_state=True)
+    ref = oracle_forward_backward(dims, master, x, T, B, idx, prob, lengths, h0, c0, bf16=True)
+    _check(got, ref, dims, BF16_TOL, state=True)
+
+
+@pytest.mark.parametrize("layers,hidden,B,T,fenced", [(5, 768, 12, 150, False), (3, 512, 48, 150, False),
+                                                      (5, 256, 40, 150, False), (4, 384, 30, 40, True)])
+def test_layers_in_one_launch_run_repeatedly(layers, hidden, B, T, fenced, monkeypatch):
+    # the layers follow one another over many steps, on one workspace, always
+    # with the same bits, and as close to one layer after another as two
+    # summation orders of the projections are
+    if fenced:
+        monkeypatch.setenv("AM_XCD_FENCED", "1")
+    dims = oracle.ModelDims(layers, 40, hidden, 72)
+    m = am.Model(dims.layers, dims.input_dim, dims.hidden, dims.classes, am.BF16)
+    say(f"layers in one launch, repeated L={layers} H={hidden} B={B}")
+    master, x, idx, prob, _, _ = _problem(dims, T, B, 6, 0.98, seed=47)
+    first = gpu_forward_backward(m, master, x, T, B, idx, prob)
+    for _ in range(3):
+        again = gpu_forward_backward(m, master, x, T, B, idx, prob)
+        for k in ("logits", "dlogits", "grads"):
+            np.testing.assert_array_equal(again[k].view(np.uint32), first[k].view(np.uint32))
+    monkeypatch.setenv("AM_RECURRENCE", "xcd")
+    one = gpu_forward_backward(m, master, x, T, B, idx, prob)
+    for k in ("logits", "grads"):
+        a, b = first[k].astype(np.float64), one[k].astype(np.float64)
+        assert np.linalg.norm(a - b) <= 1e-2 * np.linalg.norm(b)
