@@ -30,8 +30,8 @@
 // layers below.
 //
 // 5 x 768, 12 sequences of 32 frames, whole forward: 468 us layer by layer ->
-// 237.  3 x 512, 48
-// chunks of 13-40 frames, whole training step: 800 -> 706 us.
+// 212.  3 x 512, 48
+// chunks of 13-40 frames, whole training step: 800 -> 679 us.
 #include <cstdlib>
 
 #include "xcd_sync.h"
@@ -41,27 +41,33 @@ namespace {
 
 constexpr int RB = 16;  // sequences per block
 
-// Two 8-byte device-scope stores: write-through, so that another XCD's loads
-// see them once they have completed.
-__device__ __forceinline__ void store16_agent(void* dst, uint4 v) {
-  unsigned long long* p = static_cast<unsigned long long*>(dst);
-  __hip_atomic_store(p, (unsigned long long)v.x | ((unsigned long long)v.y << 32), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(p + 1, (unsigned long long)v.z | ((unsigned long long)v.w << 32), __ATOMIC_RELAXED,
+// A device-scope store: write-through, so that another XCD's loads see it once
+// it has completed.
+__device__ __forceinline__ void store8_agent(void* dst, uint2 v) {
+  __hip_atomic_store(static_cast<unsigned long long*>(dst),
+                     (unsigned long long)v.x | ((unsigned long long)v.y << 32), __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// H = 32 KS; TPW column tiles (4 units x 4 gates) per wave and k-half; the
-// last XL k-steps of a wave's successor weights sit in LDS.
+// H = 32 KS; the recurrent product as in lstm_fwd_xcd (TPW column tiles of 4
+// units x 4 gates per wave and k-half).  The successor's projections are
+// computed transposed, one tile a wave over the whole k-range (with TPW = 1 by
+// waves 4-7, which have no cells): W_x the row operand in the same unit-major
+// order, so a lane has the four gates of one (unit, sequence) in its four
+// accumulators and stores them as 8 bytes, with no exchange between waves.  The
+// last XL k-steps of these weights sit in LDS.  (Split over k-halves like the
+// recurrent product, summed and staged through LDS, a step took 3.85 us at 5 x
+// 768 and 2.6 at 5 x 512 instead of 3.3 and 2.2; the recurrence alone
+// takes 2.0 and 1.6.)
 template <int KS, int TPW, int XL>
 __global__ __launch_bounds__(512, 1) void lstm_fwd_pipe(PipeFwd a, PersistSchedule ps, XcdSync y) {
-  constexpr int KH = KS / 2, FIN = (TPW + 1) / 2, XR = KH - XL;
+  constexpr int KH = KS / 2, FIN = (TPW + 1) / 2, XR = KS - XL;
   constexpr int HS_BYTES = RB * KS * 64, RED_BYTES = 8 * TPW * 64 * 16;
   extern __shared__ __align__(16) unsigned char lds[];
   bf16_t* hl = reinterpret_cast<bf16_t*>(lds);
   f32x4_t* red = reinterpret_cast<f32x4_t*>(lds + HS_BYTES);             // [8][TPW][64]
-  Frag<bf16_t>* wxl = reinterpret_cast<Frag<bf16_t>*>(lds + HS_BYTES + RED_BYTES);  // [8][TPW][XL][64]
-  unsigned char* stC = lds + HS_BYTES + RED_BYTES + 8 * TPW * XL * 1024;
+  Frag<bf16_t>* wxl = reinterpret_cast<Frag<bf16_t>*>(lds + HS_BYTES + RED_BYTES);  // [8][XL][64]
+  unsigned char* stC = lds + HS_BYTES + RED_BYTES + 8 * XL * 1024;
   __shared__ int bad_sh;
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -77,7 +83,6 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_pipe(PipeFwd a, PersistSchedu
   const int CSB = U * 4 + 16, HSB = U * 2 + 16, GSB = U * 8 + 16;  // staged row strides
   unsigned char* stH = stC + RB * CSB;
   unsigned char* stG = stH + RB * HSB;
-  unsigned char* stP = stG + RB * GSB;  // the successor's projections, as the gates
   const bf16_t* __restrict__ Wh = static_cast<const bf16_t*>(me.Wh);
   const bf16_t* __restrict__ Wx = static_cast<const bf16_t*>(me.WxN);
   const bf16_t* __restrict__ h0 = static_cast<const bf16_t*>(me.h0);
@@ -90,22 +95,28 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_pipe(PipeFwd a, PersistSchedu
   unsigned* mine = a.pflags + slot * 32 + us;
 
   // resident weights: column c of tile n is unit j0 + 4n + c/4, gate c%4
-  Frag<bf16_t> wf[TPW][KH], wx[TPW][XR > 0 ? XR : 1];
+  const int c16 = lane & 15, kq = lane >> 4;
+  auto wrow = [&](int n) { return (int64_t)((c16 & 3) * H + j0 + 4 * n + (c16 >> 2)) * H + kq * 8; };
+  Frag<bf16_t> wf[TPW][KH], wx[XR];
 #pragma unroll
   for (int ts = 0; ts < TPW; ++ts) {
     const int t = g + 4 * ts;
-    const int c = lane & 15;
-    const int64_t row = (int64_t)((c & 3) * H + j0 + 4 * (t < ntiles ? t : 0) + (c >> 2)) * H;
+    const bf16_t* w = Wh + wrow(t < ntiles ? t : 0);
 #pragma unroll
-    for (int s = 0; s < KH; ++s) {
-      const int64_t at = row + (kh * KH + s) * 32 + (lane >> 4) * 8;
-      wf[ts][s] = frag_load<bf16_t>(Wh + at);
-      if (has_next) {
-        const Frag<bf16_t> f = frag_load<bf16_t>(Wx + at);
-        if (s < XR) wx[ts][s < XR ? s : 0] = f;
-        else wxl[((wave * TPW + ts) * XL + (s - XR)) * 64 + lane] = f;
-      }
-    }
+    for (int s = 0; s < KH; ++s) wf[ts][s] = frag_load<bf16_t>(w + (kh * KH + s) * 32);
+  }
+  const int xt = TPW == 1 ? wave - 4 : wave;  // this wave's tile of the successor's projections
+  const bool projects = has_next && xt >= 0 && xt < ntiles;
+  const int xu = j0 + 4 * (projects ? xt : 0) + kq;  // the lane's unit in it
+  float xbias[4] = {0.f, 0.f, 0.f, 0.f};
+  if (projects) {
+    const bf16_t* w = Wx + wrow(xt);
+#pragma unroll
+    for (int s = 0; s < XR; ++s) wx[s] = frag_load<bf16_t>(w + s * 32);
+#pragma unroll
+    for (int s = 0; s < XL; ++s) wxl[(wave * XL + s) * 64 + lane] = frag_load<bf16_t>(w + (XR + s) * 32);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) xbias[q] = bf16_to_f32(static_cast<const bf16_t*>(me.bN)[q * H + xu]);
   }
   const bool local = check_local(y, slot, us, members, &bad_sh);
 
@@ -117,14 +128,12 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_pipe(PipeFwd a, PersistSchedu
     return j0 + 4 * (t < ntiles ? t : 0) + ((lane & 15) >> 2);
   };
   float c_reg[FIN];
-  bf16_t h_reg[FIN], bias[FIN][4];
+  bf16_t h_reg[FIN];
 #pragma unroll
   for (int o = 0; o < FIN; ++o) {
     const int b = min(b0 + qrow, ps.B - 1), j = unit(o);
     c_reg[o] = me.c0[(int64_t)b * H + j];
     h_reg[o] = h0 ? h0[(int64_t)b * H + j] : (bf16_t)0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) bias[o][q] = has_next ? static_cast<const bf16_t*>(me.bN)[q * H + j] : (bf16_t)0;
   }
 
   // Lower layer: steps of P announced by every member, as far as this wave
@@ -159,10 +168,8 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_pipe(PipeFwd a, PersistSchedu
 
   f32x4_t acc[TPW];
   // this wave's half of the product of the h rows in LDS with its resident
-  // columns, published to red
-  auto product = [&](auto weights) {
-#pragma unroll
-    for (int ts = 0; ts < TPW; ++ts) acc[ts] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // columns
+  auto product = [&]() {
     constexpr int AB = KH > 4 ? 4 : KH;
     const int r = lane & 15;
 #pragma unroll
@@ -179,7 +186,7 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_pipe(PipeFwd a, PersistSchedu
       for (int s = 0; s < AB; ++s) {
         if (s0 + s >= KH) continue;
 #pragma unroll
-        for (int ts = 0; ts < TPW; ++ts) mma_16x16x32(acc[ts], af[s], weights(ts, s0 + s));
+        for (int ts = 0; ts < TPW; ++ts) mma_16x16x32(acc[ts], af[s], wf[ts][s0 + s]);
       }
     }
   };
@@ -214,29 +221,30 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_pipe(PipeFwd a, PersistSchedu
   // the successor's projections of the step whose h rows are in LDS: its rows
   // start at `at` (nbh sequences)
   auto project = [&](int at, int nbh) {
-    product([&](int ts, int s) {
-      return s < XR ? wx[ts][s < XR ? s : 0] : wxl[((wave * TPW + ts) * XL + (s - XR)) * 64 + lane];
-    });
-    publish();
-    __syncthreads();
+    if (!projects) return;
+    f32x4_t p[2];
+    p[0] = p[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    constexpr int AB = 4;
 #pragma unroll
-    for (int o = 0; o < FIN; ++o) {
-      float v[4];
-      gates_of(o, v);
-      if (!slot_ok(o)) continue;
+    for (int s0 = 0; s0 < KS; s0 += AB) {
+      Frag<bf16_t> hf[AB], wl[AB];
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        v[q] += bf16_to_f32(bias[o][q]);
-      *reinterpret_cast<uint2*>(stP + qrow * GSB + 8 * (unit(o) - j0)) = pack_gates(v[0], v[1], v[2], v[3]);
+      for (int s = 0; s < AB; ++s) {
+        if (s0 + s >= KS) continue;
+        const int c = (s0 + s) * 4 + kq;
+        hf[s] = *reinterpret_cast<const Frag<bf16_t>*>(hl + ((c >> 3) * RB + c16) * 64 + (((c & 7) ^ (c16 & 7)) << 3));
+        if (s0 + s >= XR) wl[s] = wxl[(wave * XL + (s0 + s - XR)) * 64 + lane];
+      }
+#pragma unroll
+      for (int s = 0; s < AB; ++s) {
+        if (s0 + s >= KS) continue;
+        mma_16x16x32(p[s & 1], s0 + s < XR ? wx[s0 + s < XR ? s0 + s : 0] : wl[s], hf[s]);
+      }
     }
-    __syncthreads();
-    const int cpr = U / 2;  // 16-byte chunks per row
-    for (int e = (int)threadIdx.x - 64; e >= 0 && e < RB * cpr; e += 448) {
-      const int r = e / cpr, c = e - r * cpr;
-      if (b0 + r < nbh)
-        store16_agent(Pn + (int64_t)(at + b0 + r) * G4 + 4 * j0 + 8 * c,
-                      *reinterpret_cast<const uint4*>(stP + r * GSB + 16 * c));
-    }
+    if (b0 + c16 < nbh)
+      store8_agent(Pn + (int64_t)(at + b0 + c16) * G4 + 4 * xu,
+                   pack_gates(p[0][0] + p[1][0] + xbias[0], p[0][1] + p[1][1] + xbias[1],
+                              p[0][2] + p[1][2] + xbias[2], p[0][3] + p[1][3] + xbias[3]));
   };
 
   wait_vm<0>();
@@ -280,7 +288,7 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_pipe(PipeFwd a, PersistSchedu
     for (int ts = 0; ts < TPW; ++ts) acc[ts] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     if (hsrc) {
       copy_h(hsrc, nbh);
-      product([&](int ts, int s) { return wf[ts][s]; });
+      product();
     }
     publish();
     __syncthreads();
@@ -381,8 +389,9 @@ bool pipe_shape(int H, int B, int layers, PipeShape* x) {
   }
   if (H % x->U != 0 || H / x->U > 32 / x->per) return false;
   x->TPW = (x->U / 4 + 3) / 4;
-  // W_h and W_x take TPW KS fragments a wave: beyond 32 a share of W_x is in LDS
-  x->XL = H <= 512 ? 0 : H == 576 ? 2 : H == 640 ? 4 : 6;
+  // beyond H = 512 the two take more than 32 fragments a wave: some of W_x's are
+  // in LDS
+  x->XL = H <= 512 ? 0 : H == 576 ? 4 : H == 640 ? 8 : 12;
   return true;
 }
 
@@ -410,11 +419,11 @@ hipError_t lstm_fwd_pipe_launch(PipeFwd a, PersistSchedule ps, XcdSync y, hipStr
   AM_PIPE_CASE(4, 1, 0) AM_PIPE_CASE(6, 1, 0) AM_PIPE_CASE(8, 1, 0) AM_PIPE_CASE(10, 1, 0)
   AM_PIPE_CASE(12, 1, 0) AM_PIPE_CASE(14, 1, 0) AM_PIPE_CASE(16, 1, 0)
   AM_PIPE_CASE(10, 2, 0) AM_PIPE_CASE(12, 2, 0) AM_PIPE_CASE(14, 2, 0) AM_PIPE_CASE(16, 2, 0)
-  AM_PIPE_CASE(18, 2, 2) AM_PIPE_CASE(20, 2, 4) AM_PIPE_CASE(22, 2, 6) AM_PIPE_CASE(24, 2, 6)
+  AM_PIPE_CASE(18, 2, 4) AM_PIPE_CASE(20, 2, 8) AM_PIPE_CASE(22, 2, 12) AM_PIPE_CASE(24, 2, 12)
   return hipSuccess;
   const int blocks = NX * x.per * (a.hidden / x.U);
-  const size_t lds = (size_t)RB * x.KS * 64 + 8 * x.TPW * 64 * 16 + 8 * x.TPW * x.XL * 1024 +
-                     (size_t)RB * (14 * x.U + 48) + (size_t)RB * (8 * x.U + 16);
+  const size_t lds = (size_t)RB * x.KS * 64 + 8 * x.TPW * 64 * 16 + 8 * x.XL * 1024 +
+                     (size_t)RB * (14 * x.U + 48);
   int dev = 0, cus = 0, per = 0;
   if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
       hipGetDevice(&dev) != hipSuccess ||
