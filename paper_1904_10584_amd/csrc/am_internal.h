@@ -293,14 +293,19 @@ hipError_t fill_zero(float* dst, int64_t n, hipStream_t s);
 hipError_t fill_zero2(float* d0, int64_t n0, float* d1, int64_t n1, hipStream_t s);
 // dst[0..n) = +0.0 when *flag (device) is nonzero, else nothing.
 hipError_t zero_if_set(const int* flag, float* dst, int64_t n, hipStream_t s);
-// Convert fp32 [rows][cols] to the activation type (h0 for the recurrence).
-hipError_t convert_rows(const float* src, void* dst, int64_t count, bool bf16, hipStream_t s);
-// Final states: out[b][j] = state at row[b] (or init[b][j] / 0 if row[b] < 0).
+// The start of a forward pass: `sync` zeroed (nsync floats), c = c0 or zero and
+// h = h0 in the activation type (if given), n elements each.
+hipError_t init_state(float* sync, int64_t nsync, const float* c0, float* c, const float* h0, void* h,
+                      int64_t n, bool bf16, hipStream_t s);
+// Final states of every layer: out[l][b][j] = state at row[b] of layer l (or
+// init[l][b][j] / 0 if row[b] < 0); layer l's rows start layer_bytes l behind
+// the first layer's.
 struct GatherState {
   const void* Hrows; bool h_bf16; const float* Crows;
+  int64_t layer_bytes;
   const float* h0; const float* c0;
   float* hT; float* cT;
-  int B, hidden;
+  int layers, B, hidden;
   int rows[256];
 };
 hipError_t gather_state(const GatherState& a, int b0, int nb, hipStream_t s);

@@ -1043,12 +1043,10 @@ am_status lstm_am_forward(const am_model* m, const void* params, const void* x,
   {
     Timed tm(AM_K_MISC, s, 0.0, 8.0 * L * B * H);
     float* c0w = at<float>(ws, w.c0);
-    if (c0) AM_TRY(hip_check(am::convert_rows(c0, c0w, L * B * H, false, s), "c0 copy"));
-    if (h0) AM_TRY(hip_check(am::convert_rows(h0, at<void>(ws, w.h0), L * B * H, bf, s), "h0 convert"));
     // a new forward + backward pair: every slot of the sync area and the
-    // barrier time-out flag (and a zero initial cell state, in the same launch)
-    AM_TRY(hip_check(am::fill_zero2(at<float>(ws, w.sync), 2 * L * sync_rounds(B) * SYNC_BYTES / 4, c0w,
-                                    c0 ? 0 : L * B * H, s), "sync and c0 clear"));
+    // barrier time-out flag with it
+    AM_TRY(hip_check(am::init_state(at<float>(ws, w.sync), 2 * L * sync_rounds(B) * SYNC_BYTES / 4, c0, c0w,
+                                    h0, at<void>(ws, w.h0), L * B * H, bf, s), "initial state"));
   }
 
   // few sequences: every layer in one launch behind the first projection
@@ -1107,26 +1105,26 @@ am_status lstm_am_forward(const am_model* m, const void* params, const void* x,
                           m->classes, true, P8 + po.bo * e, (int)sc.N, m->classes, (int)H, bf), s));
 
   if (hT || cT) {
-    for (int l = 0; l < L; ++l) {
-      for (int b0 = 0; b0 < B; b0 += 256) {
-        am::GatherState g;
-        g.Hrows = at<void>(ws, w.h[l]);
-        g.h_bf16 = bf;
-        g.Crows = at<float>(ws, w.c[l]);
-        g.h0 = h0 ? h0 + (int64_t)l * B * H : nullptr;
-        g.c0 = c0 ? c0 + (int64_t)l * B * H : nullptr;
-        g.hT = hT ? hT + (int64_t)l * B * H : nullptr;
-        g.cT = cT ? cT + (int64_t)l * B * H : nullptr;
-        g.B = B;
-        g.hidden = (int)H;
-        const int nb = B - b0 < 256 ? B - b0 : 256;
-        for (int i = 0; i < nb; ++i) {
-          const int len = sc.lens[b0 + i];
-          g.rows[i] = len > 0 ? (int)(sc.offs[len - 1] + b0 + i) : -1;
-        }
-        Timed tm(AM_K_MISC, s, 0.0, 16.0 * nb * H);
-        AM_TRY(hip_check(am::gather_state(g, b0, nb, s), "final state"));
+    for (int b0 = 0; b0 < B; b0 += 256) {
+      am::GatherState g;
+      g.Hrows = at<void>(ws, w.h[0]);
+      g.h_bf16 = bf;
+      g.Crows = at<float>(ws, w.c[0]);
+      g.layer_bytes = L > 1 ? w.h[1] - w.h[0] : 0;  // (every layer's regions are laid out alike)
+      g.h0 = h0;
+      g.c0 = c0;
+      g.hT = hT;
+      g.cT = cT;
+      g.layers = (int)L;
+      g.B = B;
+      g.hidden = (int)H;
+      const int nb = B - b0 < 256 ? B - b0 : 256;
+      for (int i = 0; i < nb; ++i) {
+        const int len = sc.lens[b0 + i];
+        g.rows[i] = len > 0 ? (int)(sc.offs[len - 1] + b0 + i) : -1;
       }
+      Timed tm(AM_K_MISC, s, 0.0, 16.0 * L * nb * H);
+      AM_TRY(hip_check(am::gather_state(g, b0, nb, s), "final state"));
     }
   }
   return AM_OK;

@@ -77,13 +77,6 @@ __global__ __launch_bounds__(256) void zero_if_set_kernel(const int* __restrict_
   for (int64_t i = threadIdx.x; i < n; i += 256) dst[i] = 0.f;
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void convert_kernel(int64_t n, const float* __restrict__ src,
-                                                      T* __restrict__ dst) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-    dst[i] = from_f32<T>(src[i]);
-}
-
 // 64x64 tiles through LDS; 256 threads, each moves 16 elements.
 template <typename T>
 __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ src,
@@ -164,22 +157,39 @@ __global__ __launch_bounds__(256) void colsum_final(const float* __restrict__ pa
 
 template <typename T>
 __global__ __launch_bounds__(256) void gather_state_kernel(GatherState a, int b0) {
-  const int bi = blockIdx.x;
+  const int bi = blockIdx.x, l = blockIdx.y;
   const int b = b0 + bi;
   const int row = a.rows[bi];
   const int H = a.hidden;
-  const T* Hr = static_cast<const T*>(a.Hrows);
+  const int64_t o = ((int64_t)l * a.B + b) * H;  // of this layer and sequence in [L][B][H]
+  const T* Hr = reinterpret_cast<const T*>(static_cast<const char*>(a.Hrows) + l * a.layer_bytes);
+  const float* Cr = reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.Crows) + l * a.layer_bytes);
   for (int j = threadIdx.x; j < H; j += 256) {
     float h, c;
     if (row >= 0) {
       h = to_f32<T>(Hr[(int64_t)row * H + j]);
-      c = a.Crows[(int64_t)row * H + j];
+      c = Cr[(int64_t)row * H + j];
     } else {
-      h = a.h0 ? a.h0[(int64_t)b * H + j] : 0.f;
-      c = a.c0 ? a.c0[(int64_t)b * H + j] : 0.f;
+      h = a.h0 ? a.h0[o + j] : 0.f;
+      c = a.c0 ? a.c0[o + j] : 0.f;
     }
-    if (a.hT) a.hT[(int64_t)b * H + j] = h;
-    if (a.cT) a.cT[(int64_t)b * H + j] = c;
+    if (a.hT) a.hT[o + j] = h;
+    if (a.cT) a.cT[o + j] = c;
+  }
+}
+
+// What a forward pass starts from, in one launch: the sync area zeroed, the
+// initial cell state copied (or zeroed) and the initial h converted.
+template <typename T>
+__global__ __launch_bounds__(256) void init_state_kernel(int64_t nsync, float* __restrict__ sync, int64_t n,
+                                                         const float* __restrict__ c0, float* __restrict__ c,
+                                                         const float* __restrict__ h0, T* __restrict__ h) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nsync || i < n; i += (int64_t)gridDim.x * 256) {
+    if (i < nsync) sync[i] = 0.f;
+    if (i < n) {
+      c[i] = c0 ? c0[i] : 0.f;
+      if (h0) h[i] = from_f32<T>(h0[i]);
+    }
   }
 }
 
@@ -216,11 +226,15 @@ hipError_t cast_f32_bf16(int64_t n, const float* src, uint16_t* dst, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t convert_rows(const float* src, void* dst, int64_t count, bool bf16, hipStream_t s) {
-  if (count <= 0) return hipSuccess;
-  const unsigned g = grid_for(count, 256);
-  if (bf16) hipLaunchKernelGGL(convert_kernel<bf16_t>, dim3(g), dim3(256), 0, s, count, src, (bf16_t*)dst);
-  else hipLaunchKernelGGL(convert_kernel<float>, dim3(g), dim3(256), 0, s, count, src, (float*)dst);
+hipError_t init_state(float* sync, int64_t nsync, const float* c0, float* c, const float* h0, void* h,
+                      int64_t n, bool bf16, hipStream_t s) {
+  const unsigned g = grid_for(n > nsync ? n : nsync, 256);
+  if (bf16)
+    hipLaunchKernelGGL(init_state_kernel<bf16_t>, dim3(g), dim3(256), 0, s, nsync, sync, n, c0, c, h0,
+                       static_cast<bf16_t*>(h));
+  else
+    hipLaunchKernelGGL(init_state_kernel<float>, dim3(g), dim3(256), 0, s, nsync, sync, n, c0, c, h0,
+                       static_cast<float*>(h));
   return hipGetLastError();
 }
 
@@ -278,8 +292,9 @@ hipError_t colsum(const void* in, int64_t rows, int cols, bool bf16, float* out,
 
 hipError_t gather_state(const GatherState& a, int b0, int nb, hipStream_t s) {
   if (nb <= 0) return hipSuccess;
-  if (a.h_bf16) hipLaunchKernelGGL(gather_state_kernel<bf16_t>, dim3(nb), dim3(256), 0, s, a, b0);
-  else hipLaunchKernelGGL(gather_state_kernel<float>, dim3(nb), dim3(256), 0, s, a, b0);
+  const dim3 grid(nb, a.layers);
+  if (a.h_bf16) hipLaunchKernelGGL(gather_state_kernel<bf16_t>, grid, dim3(256), 0, s, a, b0);
+  else hipLaunchKernelGGL(gather_state_kernel<float>, grid, dim3(256), 0, s, a, b0);
   return hipGetLastError();
 }
 
