@@ -1231,7 +1231,10 @@ am_status lstm_am_backward(const am_model* m, const void* params, const void* x,
         if (!used) tm.cancel();
       }
     }
-    if (!used && !bf) {  // (the bf16 per-step path multiplies by Wh itself)
+    // (per step in bf16: the fused step reads W_h^T, the split product W_h)
+    const bool fused = !used && bf && sc.N > 0 &&
+                       am::lstm_bwd_step_fused_covers((int)H, (int)sc.counts[0]);
+    if (!used && (!bf || fused)) {
       Timed tm(AM_K_MISC, s, 0.0, 2.0 * G * H * e);
       AM_TRY(hip_check(am::transpose(P8 + po.wh[l] * e, WhT, (int)G, (int)H, bf, s), "Wh transpose"));
     }
@@ -1253,6 +1256,12 @@ am_status lstm_am_backward(const am_model* m, const void* params, const void* x,
       a.nb = (int)nb;
       a.hidden = (int)H;
       a.bf16 = bf;
+      if (fused && am::lstm_bwd_step_fused_covers((int)H, (int)nb)) {
+        Timed tm(AM_K_LSTM_BWD, s, 2.0 * nbn * G * H,
+                 (double)(nbn * G + G * H) * e + (double)nb * (H * (e + 16.0) + G * 2 * e));
+        AM_TRY(hip_check(am::lstm_bwd_step_fused_launch(a, s), "lstm backward step (fused)"));
+        continue;
+      }
       if (bf) {
         // dA_{t+1} Wh as a batched product (few rows: square tiles), then
         // the cell backward
