@@ -112,8 +112,10 @@ struct PersistFwd {
   void* H; void* Hs; float* C; void* G;  // [N][H], [N][H], [N][H], [N][4H] (written)
   unsigned* counters;  // one per block of 64 sequences, zero at launch
   int* err;            // set to 1 if a step barrier timed out
+  void* ring;          // [RING_SLOTS][B][H] scratch of the XCD-local exchange
   int hidden;
 };
+constexpr int RING_SLOTS = 4;  // (a power of two)
 struct PersistBwd {
   const void* Wh;      // [4H][H]
   const void* WhT;     // [H][4H] (the XCD-local kernel reads this layout)

@@ -405,6 +405,7 @@ am_status forward_recurrence(const FwdLayer& f, const Schedule& sc, bool bf, int
     pa.G = f.G;
     pa.counters = static_cast<unsigned*>(f.sync);
     pa.err = f.err;
+    pa.ring = bf ? f.pre : nullptr;  // (RING_SLOTS rows of H bf16 in 4H fp32)
     pa.hidden = (int)H;
     const am::PersistSchedule ps = persist_schedule(sc);
     const double flops = 2.0 * sc.N * G * H;

@@ -12,14 +12,19 @@
 //     round-robin); at start every workgroup records its XCC id and, unless
 //     every block really is on one XCD, the kernel falls back to
 //     device-scope release/acquire for its whole run;
-//   * the step barrier is one 128-byte flag line per block: every member
+//   * backward, and forward where a block spans XCDs, the step barrier is one
+//     128-byte flag line per block: every member
 //     stores its count of completed steps in its own word once its stores
 //     of the step have completed, and one wave polls the line; within one
 //     XCD both stay in its L2 (a store that the L1 passes through, polled
 //     with non-temporal loads, which the L1 does not serve from a kept
 //     line), a block spanning XCDs uses device-scope accesses and fences;
-//   * every exchanged row is written once and read only after it was written,
-//     so no consumer's L1 can hold a stale copy.
+//     every row exchanged that way is written once and read only after it was
+//     written, so no consumer's L1 can hold a stale copy;
+//   * forward, within one XCD, the data is its own flag: h goes through a ring
+//     of four slots in scratch memory that stays in the L2, where a value not
+//     yet written is all ones (no h is); the readers poll the rows themselves,
+//     which saves the wait for the stores, the flag's way and a second read.
 // A workgroup owns U hidden units (U % 4 == 0) of one block of RB sequences
 // (RB = 16 or 32).  The forward product keeps the workgroup's 4U columns of
 // W_h resident in registers in unit-major, gate-minor order, so a 16-column
@@ -35,6 +40,47 @@
 namespace am {
 namespace {
 
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+
+// Barrier that orders LDS only: loads and stores stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Two numbers to bf16 (round to nearest even) by the conversion instruction,
+// a at the low end.
+__device__ __forceinline__ uint32_t cvt_bf16x2(float a, float b) {
+  typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b16x2));
+}
+__device__ __forceinline__ uint2 cvt_gates(float i, float f, float g, float o) {
+  return make_uint2(cvt_bf16x2(i, f), cvt_bf16x2(g, o));
+}
+
+// 4x4 transpose within each quad of lanes: out[q] of lane l is v[l % 4] of
+// lane (l & ~3) + q.
+__device__ __forceinline__ void quad_transpose(f32x4_t v, int lane, float* out) {
+  auto swap = [](float x, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  using X1 = std::integral_constant<int, 0xB1>;  // lane ^ 1
+  using X2 = std::integral_constant<int, 0x4E>;  // lane ^ 2
+  const bool o1 = lane & 1, o2 = lane & 2;
+  // (the swaps by every lane, before the selections)
+  const float s0 = swap(v[0], X1{}), s1 = swap(v[1], X1{}), s2 = swap(v[2], X1{}), s3 = swap(v[3], X1{});
+  const float a0 = o1 ? s1 : v[0], a1 = o1 ? v[1] : s0, a2 = o1 ? s3 : v[2], a3 = o1 ? v[3] : s2;
+  const float t0 = swap(a0, X2{}), t1 = swap(a1, X2{}), t2 = swap(a2, X2{}), t3 = swap(a3, X2{});
+  out[0] = o2 ? t2 : a0;
+  out[1] = o2 ? t3 : a1;
+  out[2] = o2 ? a2 : t0;
+  out[3] = o2 ? a3 : t1;
+}
+
 // ----------------------------------------------------------------- forward --
 // Eight waves, two per SIMD (a single wave can issue independent MFMAs at
 // about 87 % of the peak, but not also cover its own LDS and memory waits).
@@ -42,15 +88,25 @@ namespace {
 // (row tile t % MT, column tile t / MT; all tiles of a group share row tile
 // g % MT); k-half kh = wave / 4 multiplies k-steps [kh KS/2, (kh+1) KS/2).
 // The W_h fragments of a wave's tiles and k-steps stay in its registers for
-// the whole launch.  Each step wave 0 polls the step barrier and waves 1-7
-// copy the block's rows of h_{t-1} to LDS with direct loads (whole 128-byte
-// lines), laid out line-major
+// the whole launch.  Each step waves 0-3 read the block's rows of h_{t-1} from
+// the ring until all are there and put them into LDS, line-major
 // [H/64 lines][RB rows][128 B] with the 16-byte chunks of a row XOR-swizzled
-// by row, and read back as MFMA fragments.  The two k-halves of a group
-// publish their partial tiles to LDS: the k-half-0 wave finishes the first
-// ceil(TPW/2) tiles, the k-half-1 wave the rest.  A step is signalled as soon
-// as its h stores (the only exchanged data) are complete; the cell state,
-// gate and h_{t-1} copies are stored after the signal.
+// by row, from where they are read as MFMA fragments; waves 4-7 write the
+// step before out (cell states, gates, h, h_{t-1}: staged as rows in LDS, so
+// that they go as 16-byte chunks) and fetch the next step's input projections
+// into LDS.  Without the ring wave 0 polls the step barrier and waves 1-7
+// copy the rows with direct loads.  The two k-halves of a group exchange
+// partial tiles through LDS: the k-half-0 wave finishes the first
+// ceil(TPW/2) tiles, the k-half-1 wave the rest.
+//
+// What bounds a step is its chain, about 6600 clocks for 16 rows x 48 units of
+// H = 768: sending and polling h 2300, products 1500 (1150 of MFMA issue), the
+// partial tiles 500, cells 1500 (vector instructions: two waves per SIMD, four
+// clocks each).  Before the ring, with each lane's projections as 2-byte loads
+// (1024 clocks of line look-ups a step), partial tiles read transposed from
+// LDS (bank conflicts) and bf16 rounding in integer steps it was 7900: 231 us
+// for 64 steps of 256 sequences, now 187; 1500 steps of 128 sequences 4.2 ms,
+// now 3.8.
 template <int MT, int KS, int TPW, bool STG>
 __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSchedule ps, XcdSync y) {
   constexpr int RB = 16 * MT;             // sequences per block
@@ -58,15 +114,16 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
   constexpr int FIN = (TPW + 1) / 2;      // tiles finished by the k-half-0 wave
   constexpr int HS_BYTES = RB * KS * 64;  // the block's h rows: RB x H bf16
   static_assert(KS % 2 == 0, "H must be a multiple of 64");
+  constexpr bool RING = STG && MT == 1;   // blocks whose exchange goes through the ring
   extern __shared__ __align__(16) unsigned char lds[];
   bf16_t* hl = reinterpret_cast<bf16_t*>(lds);
-  f32x4_t* red = reinterpret_cast<f32x4_t*>(lds + HS_BYTES);  // [8][TPW][64]
-  // STG (U % 8 == 0): the block's cell states, h_{t-1} copies and gates of
+  f32x4_t* red = reinterpret_cast<f32x4_t*>(lds + HS_BYTES);  // [8][FIN][64]
+  // STG (U % 8 == 0): the block's cell states, h, h_{t-1} copies and gates of
   // the step, staged as rows of the unit slice (strides padded by 16 bytes,
   // which spreads a write's 16 rows over the LDS banks) and written out by
-  // waves 1-7 after the signal as 16-byte row chunks: about 100 cache lines
+  // waves 4-7 in the next step as 16-byte row chunks: about 100 cache lines
   // per step instead of 16 per store instruction (768).
-  unsigned char* stC = lds + HS_BYTES + 8 * TPW * 64 * 16;
+  unsigned char* stC = lds + HS_BYTES + 8 * FIN * 64 * 16;
   __shared__ int bad_sh;
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -81,6 +138,9 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
   const int CSB = U * 4 + 16, HSB = U * 2 + 16, GSB = U * 8 + 16;  // staged row strides
   unsigned char* stH = stC + RB * CSB;
   unsigned char* stG = stH + RB * HSB;
+  unsigned char* stN = stG + RB * GSB;  // h_t (ring exchange)
+  // STG: two steps' input projections, [gate][8 units][row] in 16-byte pieces
+  bf16_t* stP = reinterpret_cast<bf16_t*>(stN + RB * HSB);
   const bf16_t* __restrict__ P = static_cast<const bf16_t*>(a.P);
   const bf16_t* __restrict__ Wh = static_cast<const bf16_t*>(a.Wh);
   const bf16_t* __restrict__ h0 = static_cast<const bf16_t*>(a.h0);
@@ -100,7 +160,25 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
     for (int s = 0; s < KH; ++s)
       wf[ts][s] = frag_load<bf16_t>(Wh + (int64_t)row * H + (kh * KH + s) * 32 + (lane >> 4) * 8);
   }
+  bf16_t* const hring = static_cast<bf16_t*>(a.ring);
+  const int64_t slot = (int64_t)ps.B * H;  // elements of a ring slot
+  // The 16-byte piece of this member's slice of a slot that this thread (of
+  // the first 2U) writes and unwrites: row pr, chunk pc.
+  const int u8 = STG ? U / 8 : 1;
+  const int pr = threadIdx.x / u8, pc = threadIdx.x % u8;
+  const bool piece_ok = RING && pr < RB && b0 + pr < ps.B;
+  const uint32_t piece = (uint32_t)((b0 + pr) * H + j0 + 8 * pc);
+  const u32x4_t unset = {~0u, ~0u, ~0u, ~0u};
+  if (piece_ok && hring) {
+#pragma unroll
+    for (int q = 0; q < RING_SLOTS; ++q) *reinterpret_cast<u32x4_t*>(hring + q * slot + piece) = unset;
+  }
+  if (RING) {
+    __builtin_amdgcn_s_waitcnt(0);  // in the L2 before the XCC id is published
+    __syncthreads();
+  }
   const bool local = check_local(y, blk, us, members, &bad_sh);
+  const bool ring = RING && local && hring != nullptr;
 
   // The tiles this wave finishes ("own slots" o < FIN): tile index
   // ts = o (k-half 0) or FIN + o (k-half 1).  The lane's cells in tile t:
@@ -142,47 +220,164 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
       store_gates(Gb + (int64_t)row * G4, j, gv[o]);
     }
   };
-  // every load so far (weights, state) is complete here, so the compiler
-  // keeps no waits for them inside the loop
-  wait_vm<0>();
-  int nb = ps.B, off = 0, off_prev = 0;
-  for (int t = 0; t < ps.T; ++t) {
-    nb = active_down(ps, nb, t);
-    if (b0 >= nb) break;  // this block of sequences has ended for good
-
-    // Input projections of this lane's cells (independent of the exchange;
-    // clamped, unmasked loads so that they issue back to back).  Waves 1-7
-    // issue them before the exchange, so that they have the poll's time to
-    // arrive; the polling wave issues its own after the poll, which would
-    // otherwise wait for them (its memory counter retires in order).
-    bf16_t pin[FIN][4];
-    auto load_pin = [&]() {
-      const bf16_t* prow = P + (int64_t)(off + min(b0 + qrow, nb - 1)) * G4;
+  // Input projections of the block's cells (independent of the exchange),
+  // requested one step ahead.  STG: by waves 4-7 into LDS, 16 rows x 16 bytes
+  // x 4 an instruction (an eighth of the cache lines that 2-byte loads of each
+  // lane's cells touch).  Else by each lane, right after the exchange, so that
+  // the next exchange's loads, which come back in order behind them, find them
+  // arrived; clamped, unmasked loads, so that they issue back to back.
+  constexpr int PI = STG ? 2 : 1;  // instructions per wave (U <= 64)
+  int pcol[PI];
+#pragma unroll
+  for (int i = 0; i < PI; ++i) {
+    const int cg = (i * 4 + (wave & 3)) * 4 + (lane >> 4);  // gate and 8-unit group
+    pcol[i] = cg / u8 * H + j0 + cg % u8 * 8;
+  }
+  bf16_t pnext[FIN][4];
+  auto load_pin = [&](int t_, int o_, int n_) {
+    if constexpr (STG) {
+      if (wave < 4 || b0 >= n_) return;
+      const bf16_t* base = P + (int64_t)o_ * G4;
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        const uint32_t row = (uint32_t)(min(b0 + 16 * m + (lane & 15), n_ - 1) * G4);
+#pragma unroll
+        for (int i = 0; i < PI; ++i) {
+          const int n = i * 4 + (wave & 3);
+          if (n >= U / 8) continue;
+          dma16(base + (row + (uint32_t)pcol[i]),
+                __builtin_amdgcn_readfirstlane(lds_address(stP + (((t_ & 1) * MT + m) * (U / 8) + n) * 512)));
+        }
+      }
+    } else {
+      const bf16_t* base = P + (b0 < n_ ? (int64_t)o_ * G4 : 0);
+      const uint32_t row = b0 < n_ ? (uint32_t)(min(b0 + qrow, n_ - 1) * G4) : 0u;
 #pragma unroll
       for (int o = 0; o < FIN; ++o)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) pin[o][q] = prow[q * H + unit(o)];
-    };
-    if (wave != 0) load_pin();
-
-    f32x4_t acc[TPW];
+        for (int q = 0; q < 4; ++q) pnext[o][q] = base[row + (uint32_t)(q * H + unit(o))];
+    }
+  };
+  // STG: a finished step's staged rows, written by waves 4-7 (the other four
+  // fetch h) as 16-byte chunks, an equal share each: the gates by waves 4 and
+  // 5, C by wave 6, Hs and with the ring H by wave 7.  Chunk e of a section
+  // with cpr chunks per row is row e / cpr (by a multiply: e is small).
+  auto write_staged = [&](int off_w, int nb_w) {
+    // (two sections of one shape, the second one's chunks after the first's)
+    auto sections = [&](const unsigned char* st, int stride, int cpr, int first, int step, int n, char* dst,
+                        char* dst2, uint32_t ld) {
+      const uint32_t inv = (65536u + cpr - 1) / cpr;
+      for (int e0 = lane + first; e0 < n; e0 += 4 * step) {
+        uint4 v[4];
+        char* d[4];
+        bool ok[4];
 #pragma unroll
-    for (int ts = 0; ts < TPW; ++ts) acc[ts] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < 4; ++k) {
+          const int e = min(e0 + k * step, n - 1);
+          const bool two = e >= RB * cpr;
+          const int f = two ? e - RB * cpr : e;
+          const int r = (int)((uint32_t)f * inv >> 16), c = f - r * cpr;
+          v[k] = *reinterpret_cast<const uint4*>(st + (two ? stN - stH : 0) + r * stride + 16 * c);
+          d[k] = (two ? dst2 : dst) + (uint32_t)(r * ld + 16 * c);
+          ok[k] = e0 + k * step < n && b0 + r < nb_w;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (ok[k]) *reinterpret_cast<uint4*>(d[k]) = v[k];
+      }
+    };
+    const int64_t row0 = off_w + b0, at = row0 * H + j0;
+    if (wave < 6) {
+      sections(stG, GSB, U / 2, (wave - 4) * 64, 128, RB * U / 2, reinterpret_cast<char*>(Gb + 4 * at), nullptr, 2 * G4);
+    } else if (wave == 6) {
+      sections(stC, CSB, U / 4, 0, 64, RB * U / 4, reinterpret_cast<char*>(a.C + at), nullptr, 4 * H);
+    } else {
+      sections(stH, HSB, U / 8, 0, 64, (ring ? 2 : 1) * RB * U / 8, reinterpret_cast<char*>(Hs + at),
+               reinterpret_cast<char*>(Hb + at), 2 * H);
+    }
+  };
+  int nb = active_down(ps, ps.B, 0), off = 0, off_prev = 0, nb_prev = 0;
+  load_pin(0, 0, nb);
+  unsigned spins = 0;
+  // every load so far (weights, state, the first projections) is complete
+  // here, so the compiler keeps no waits for them inside the loop
+  wait_vm<0>();
+  for (int t = 0; t < ps.T; ++t) {
+    if (b0 >= nb) break;  // this block of sequences has ended for good
+    const int nb_next = t + 1 < ps.T ? active_down(ps, nb, t + 1) : 0;
+
+    bf16_t pin[FIN][4];
+    if constexpr (STG) {
+      if (wave >= 4) wait_vm_asm<0>();  // this step's projections, asked for a step ago
+    } else {
+#pragma unroll
+      for (int o = 0; o < FIN; ++o)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) pin[o][q] = pnext[o][q];
+    }
+    constexpr int RG = RB / 8, NQ = (KS / 2) * RG;  // pieces of 8 rows x 128 bytes
     const bf16_t* hsrc = h0;
-    if (t > 0) {
-      xwait(y, local, blk, members, (unsigned)t);
-      hsrc = Hb + (int64_t)off_prev * H;
-    }
-    if (wave == 0 && drow >= 0) {
-      post_stores(drow, dc, dg, dh);
-      drow = -1;
-    }
-    if (wave == 0) load_pin();
-    if (hsrc) {
-      // the block's rows of h_{t-1} (inactive rows read an active one) to
-      // LDS, by waves 1-7
-      constexpr int RG = RB / 8, NQ = (KS / 2) * RG;
-      if (wave > 0) {
+    if (STG && t > 0 && wave >= 4) write_staged(off_prev, nb_prev);
+    if (ring && t > 0) {
+      if constexpr (RING) {
+        if (wave < 4) {
+          // send this member's h_{t-1}
+          if (piece_ok && b0 + pr < nb_prev)
+            *reinterpret_cast<u32x4_t*>(hring + ((t - 1) & (RING_SLOTS - 1)) * slot + piece) =
+                *reinterpret_cast<const u32x4_t*>(stN + pr * HSB + 16 * pc);
+          // waves 0-3 read the ring until every value has been written, then
+          // put the rows (inactive rows read an active one) into LDS
+          // (wave w: rows 8 (w % 2) .., lines w / 2, w / 2 + 2, ..; an odd
+          // number of lines has its last fetched by all four)
+          constexpr int PQ = (NQ + 3) / 4;
+          const int r = (wave & 1) * 8 + (lane >> 3), l0 = wave >> 1;
+          auto line = [&](int i) { return NQ % 4 != 0 && i == PQ - 1 ? KS / 2 - 1 - l0 : 2 * i; };  // beyond l0
+          const bf16_t* hs = hring + ((t - 1) & (RING_SLOTS - 1)) * slot;
+          const uint32_t at = (uint32_t)(min(b0 + r, nb - 1) * H + l0 * 64 + (lane & 7) * 8);
+          u32x4_t v[PQ];
+          for (;;) {
+#pragma unroll
+            for (int i = 0; i < PQ; ++i)
+              v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(hs + (at + (uint32_t)(line(i) * 64))));
+            wait_vm_asm<0>();  // (the stores issued before, too)
+            u16x2_t top = 0;  // (all ones, an unwritten value, is the largest)
+#pragma unroll
+            for (int i = 0; i < PQ; ++i)
+#pragma unroll
+              for (int k = 0; k < 4; ++k)
+                top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2_t, (uint32_t)v[i][k]));
+            if (!__any(top[0] == 0xffffu || top[1] == 0xffffu)) break;
+            if (++spins > SPIN_LIMIT) {  // (over all steps: after a time-out none waits again)
+              if (lane == 0) __hip_atomic_store(y.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              break;
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < PQ; ++i)
+            *reinterpret_cast<u32x4_t*>(hl + ((l0 + line(i)) * RB + r) * 64 + (((lane & 7) ^ (r & 7)) << 3)) = v[i];
+        }
+      }
+      load_pin(t + 1, off + nb, nb_next);
+      lds_barrier();
+      // All four waves have seen their part of h_{t-1}, so every member has
+      // sent it and has read h_{t-2} before: unwrite this member's piece of
+      // h_{t-2}.  (A wave's own poll covers some members only.)  That store
+      // is complete before this wave's poll of step t + 1 ends, so before
+      // h_{t+1} is sent, and a member polls the slot again only after it has
+      // received h_{t+1}.
+      if (t > 1 && piece_ok) *reinterpret_cast<u32x4_t*>(hring + ((t - 2) & (RING_SLOTS - 1)) * slot + piece) = unset;
+    } else {
+      if (t > 0) {
+        xwait(y, local, blk, members, (unsigned)t);
+        hsrc = Hb + (int64_t)off_prev * H;
+      }
+      if (wave == 0 && drow >= 0) {
+        post_stores(drow, dc, dg, dh);
+        drow = -1;
+      }
+      if (hsrc && wave > 0) {
+        // the block's rows of h_{t-1} (inactive rows read an active one) to
+        // LDS, by waves 1-7
         for (int q = wave - 1; q < NQ; q += 7) {
           const int line = q / RG, rg = q % RG;
           const int r = rg * 8 + (lane >> 3);
@@ -192,10 +387,16 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
         }
         wait_vm<0>();
       }
-      __syncthreads();
+      load_pin(t + 1, off + nb, nb_next);
+      lds_barrier();
+    }
+    f32x4_t acc[TPW];
+#pragma unroll
+    for (int ts = 0; ts < TPW; ++ts) acc[ts] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (t > 0 || hsrc) {
       // A fragments in batches of up to four, each batch read before its
       // MFMAs (the resident weights leave room for four in registers)
-      constexpr int AB = KH > 4 ? 4 : KH;
+      constexpr int AB = TPW * KH > 32 ? 3 : KH > 4 ? 4 : KH;
       const int r = mw * 16 + (lane & 15);
 #pragma unroll
       for (int s0 = 0; s0 < KH; s0 += AB) {
@@ -219,22 +420,40 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
       }
     }
 
-    // both k-halves publish all their partial tiles; each lane then reads
-    // the two partials of its cells straight in transposed order (4x4 quads:
-    // lane l takes, for row 4(l/16) + l%4, the 4 gates of its unit from
-    // lanes (l & ~3) + q).  Selecting among the accumulators by the runtime
-    // k-half instead would index them dynamically: compare/select chains.
+    // Each k-half publishes the partial tiles that the other finishes and adds
+    // the other's to its own.  A 4x4 transpose over quads of lanes (DPP) then
+    // gives lane l, for row 4(l/16) + l%4, the 4 gates of its unit from lanes
+    // (l & ~3) + q.
+    f32x4_t own[FIN];
+    if (kh == 0) {
 #pragma unroll
-    for (int ts = 0; ts < TPW; ++ts) red[(wave * TPW + ts) * 64 + lane] = acc[ts];
-    __syncthreads();
+      for (int o = 0; o < FIN; ++o) {
+        own[o] = acc[o];
+        if (FIN + o < TPW) red[(g * FIN + o) * 64 + lane] = acc[FIN + o];
+      }
+    } else {
+#pragma unroll
+      for (int o = 0; o < FIN; ++o) {
+        own[o] = FIN + o < TPW ? acc[FIN + o] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        red[((g + 4) * FIN + o) * 64 + lane] = acc[o];
+      }
+    }
+    if constexpr (STG) {
+#pragma unroll
+      for (int o = 0; o < FIN; ++o) {
+        const int u = unit(o) - j0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          pin[o][q] = stP[((((t & 1) * MT + mw) * 4 + q) * (U / 8) + (u >> 3)) * 128 + (lane >> 4) * 32 + (lane & 3) * 8 + (u & 7)];
+      }
+    }
+    lds_barrier();
     float gate[FIN][4];
 #pragma unroll
     for (int o = 0; o < FIN; ++o) {
-      const int ts = slot_ts(o) % TPW;
-      const float* p0 = reinterpret_cast<const float*>(red + (g * TPW + ts) * 64 + (lane & ~3));
-      const float* p1 = reinterpret_cast<const float*>(red + ((g + 4) * TPW + ts) * 64 + (lane & ~3));
-#pragma unroll
-      for (int q = 0; q < 4; ++q) gate[o][q] = p0[4 * q + (lane & 3)] + p1[4 * q + (lane & 3)];
+      // (k-half 1's slots past the last tile read unset memory; unused)
+      const f32x4_t v = own[o] + red[((g + 4 * (1 - kh)) * FIN + o) * 64 + lane];
+      quad_transpose(v, lane, gate[o]);
     }
 
     const int b = b0 + qrow;
@@ -249,56 +468,28 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
       gate[o][2] = tanh_f(gate[o][2] + bf16_to_f32(pin[o][2]));
       gate[o][3] = sigm(gate[o][3] + bf16_to_f32(pin[o][3]));
       cnew[o] = gate[o][1] * c_reg[o] + gate[o][0] * gate[o][2];
-      const bf16_t h = f32_to_bf16(gate[o][3] * tanh_f(cnew[o]));
+      bf16_t h = (bf16_t)cvt_bf16x2(gate[o][3] * tanh_f(cnew[o]), 0.f);
+      if ((h & 0x7fffu) > 0x7f80u) h = 0x7fc0u;  // one NaN: all ones is the ring's "not yet"
       if (row_ok && slot_ok(o)) {
-        Hb[(int64_t)(off + b) * H + unit(o)] = h;
+        if (!ring) Hb[(int64_t)(off + b) * H + unit(o)] = h;
         c_reg[o] = cnew[o];
         h_reg[o] = h;
         if constexpr (STG) {
           const int u = unit(o) - j0;
+          *reinterpret_cast<bf16_t*>(stN + qrow * HSB + 2 * u) = h;
           *reinterpret_cast<float*>(stC + qrow * CSB + 4 * u) = cnew[o];
           *reinterpret_cast<bf16_t*>(stH + qrow * HSB + 2 * u) = hprev[o];
           *reinterpret_cast<uint2*>(stG + qrow * GSB + 8 * u) =
-              pack_gates(gate[o][0], gate[o][1], gate[o][2], gate[o][3]);
+              cvt_gates(gate[o][0], gate[o][1], gate[o][2], gate[o][3]);
         }
       }
     }
-    xsignal(y, local, blk, us, (unsigned)(t + 1));  // h stores complete; its barrier also orders the LDS reuse
-    // stores only the backward pass reads
-    if constexpr (STG) {
-      // 16-byte chunks of the staged rows: C, then Hs, then G; chunk e of a
-      // section with cpr chunks per row is row e / cpr (by a multiply: e is
-      // small), chunk e % cpr
-      if (wave > 0) {
-        const int cC = U / 4, cH = U / 8, cG = U / 2;
-        const int nC = RB * cC, nH = RB * cH, nG = RB * cG;
-        auto divr = [](int e, int d) { return (int)(((unsigned)e * ((65536u + d - 1) / d)) >> 16); };
-        for (int e = threadIdx.x - 64; e < nC + nH + nG; e += 448) {
-          int r, c;
-          const unsigned char* src;
-          void* dst;
-          if (e < nC) {
-            r = divr(e, cC); c = e - r * cC;
-            src = stC + r * CSB + 16 * c;
-            dst = a.C + (int64_t)(off + b0 + r) * H + j0 + 4 * c;
-          } else if (e < nC + nH) {
-            const int f = e - nC;
-            r = divr(f, cH); c = f - r * cH;
-            src = stH + r * HSB + 16 * c;
-            dst = Hs + (int64_t)(off + b0 + r) * H + j0 + 8 * c;
-          } else {
-            const int f = e - nC - nH;
-            r = divr(f, cG); c = f - r * cG;
-            src = stG + r * GSB + 16 * c;
-            dst = Gb + (int64_t)(off + b0 + r) * G4 + 4 * j0 + 8 * c;
-          }
-          if (b0 + r < nb) *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
-        }
-      }
-    } else {
+    if (ring) lds_barrier();  // the staged rows
+    else xsignal(y, local, blk, us, (unsigned)(t + 1));  // h stores complete; its barrier also orders the LDS reuse
+    if constexpr (!STG) {  // stores only the backward pass reads
     uint2 gp[FIN];
 #pragma unroll
-    for (int o = 0; o < FIN; ++o) gp[o] = pack_gates(gate[o][0], gate[o][1], gate[o][2], gate[o][3]);
+    for (int o = 0; o < FIN; ++o) gp[o] = cvt_gates(gate[o][0], gate[o][1], gate[o][2], gate[o][3]);
     if (wave != 0) {
       if (row_ok) post_stores(off + b, cnew, gp, hprev);
     } else if (row_ok) {
@@ -312,9 +503,12 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
     }
     }
     off_prev = off;
+    nb_prev = nb;
     off += nb;
+    nb = nb_next;
   }
   if (wave == 0 && drow >= 0) post_stores(drow, dc, dg, dh);
+  if (STG && wave >= 4 && nb_prev > 0) write_staged(off_prev, nb_prev);
 }
 
 // ---------------------------------------------------------------- backward --
@@ -688,9 +882,10 @@ hipError_t lstm_fwd_xcd_launch(PersistFwd a, PersistSchedule ps, XcdSync y, hipS
   y.units = x.U;
   y.fenced = fenced_forced() ? 1 : 0;
   const int blocks = NX * x.BPX * (a.hidden / x.U);
-  // h rows, partial tiles, and (U % 8 == 0) the staged rows of C, Hs and G
-  const size_t lds = (size_t)16 * x.MT * x.KS * 64 + 8 * x.TPW * 64 * 16 +
-                     (x.U % 8 == 0 ? (size_t)16 * x.MT * (14 * x.U + 48) : 0);
+  // h rows, partial tiles, and (U % 8 == 0) the staged rows of C, Hs, G and h
+  // and two steps' projections
+  const size_t lds = (size_t)16 * x.MT * x.KS * 64 + 8 * ((x.TPW + 1) / 2) * 64 * 16 +
+                     (x.U % 8 == 0 ? (size_t)16 * x.MT * (32 * x.U + 64) : 0);
   for (int r = 0; r < x.rounds; ++r) {
     xcd_round(x, r, ps, y);
     void* args[] = {&a, &ps, &y};

@@ -81,6 +81,28 @@ def test_bf16_recurrence_shapes_run_repeatedly(hidden, B):
             np.testing.assert_array_equal(again[k].view(np.uint32), first[k].view(np.uint32))
 
 
+# the forward exchange within an XCD (rows polled in a ring) against the fenced
+# one (flags), over enough steps that the ring's slots turn over and members
+# drift: the same bits.  Odd and even numbers of 128-byte lines per row, one and
+# two blocks per XCD, sequences that end at different steps
+@pytest.mark.parametrize("hidden,B", [(64, 9), (192, 150), (320, 40), (512, 140), (576, 17), (768, 128), (768, 200),
+                                      (832, 5), (1024, 300)])
+def test_ring_exchange_equals_flags(hidden, B, monkeypatch):
+    dims = oracle.ModelDims(1, 24, hidden, 40)
+    T = 180
+    lengths = np.sort(np.random.default_rng(hidden + B).integers(T // 3, T + 1, B))[::-1].astype(np.int32)
+    lengths[0] = T
+    m = am.Model(dims.layers, dims.input_dim, dims.hidden, dims.classes, am.BF16)
+    say(f"ring exchange H={hidden} B={B}")
+    monkeypatch.setenv("AM_RECURRENCE", "xcd")
+    master, x, idx, prob, h0, c0 = _problem(dims, T, B, 6, 0.98, lengths, seed=59, state=True)
+    got = gpu_forward_backward(m, master, x, T, B, idx, prob, lengths, h0, c0, want_state=True)
+    monkeypatch.setenv("AM_XCD_FENCED", "1")
+    ref = gpu_forward_backward(m, master, x, T, B, idx, prob, lengths, h0, c0, want_state=True)
+    for k in ref:
+        np.testing.assert_array_equal(np.asarray(got[k]), np.asarray(ref[k]))
+
+
 # every layer in one launch: each instantiation, an XCD or half of one per
 # (layer, block), up to every slot taken; more blocks than slots (the last) go
 # layer by layer
