@@ -31,7 +31,45 @@ __device__ __forceinline__ BmufOne bmuf_one(double s, float wg, float d0, double
   return BmufOne{(float)w, (float)d};
 }
 
-template <bool ALIGNED>
+// Accesses of four elements at the elements' own alignment (the rows of a
+// model array of odd length start anywhere), which the memory instructions
+// take: 16 bytes from any multiple of 4.
+typedef f32x4_t f32x4_u __attribute__((aligned(4)));
+typedef uint16_t u16x4_t __attribute__((ext_vector_type(4)));
+typedef u16x4_t u16x4_u __attribute__((aligned(2)));
+
+template <bool STREAM>
+__device__ __forceinline__ f32x4_t load4(const float* p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const f32x4_u*>(p));
+  else return *reinterpret_cast<const f32x4_u*>(p);
+}
+template <bool STREAM>
+__device__ __forceinline__ void store4(float* p, f32x4_t v) {
+  if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<f32x4_u*>(p));
+  else *reinterpret_cast<f32x4_u*>(p) = v;
+}
+
+// Four elements of K models added to s in order, the K loads requested before
+// the first add.
+template <int K, bool STREAM>
+__device__ __forceinline__ void add_models(double* s, const float* m, int64_t stride) {
+#pragma clang fp contract(off)
+  f32x4_t v[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) v[k] = load4<STREAM>(m + k * stride);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] = s[q] + (double)v[k][q];
+}
+
+// Four elements a thread, the whole array in one grid (8192 workgroups in a
+// loop ended unevenly: 258 us below).  What bounds it: HBM.  STREAM: every
+// access non-temporal (see the launch).  24,145,848 elements, 8 addends, both
+// restart copies (1.30 GB): 247 -> 229 us; 10,000,001 elements, 3 addends, whose
+// rows start off the 16-byte grid (one element at a time before): 216 -> 59.
+template <bool STREAM>
 __global__ __launch_bounds__(256) void bmuf_kernel(int64_t n, int count, double workers,
                                                    const float* models,
                                                    int64_t stride, float* wg, float* delta,
@@ -40,33 +78,35 @@ __global__ __launch_bounds__(256) void bmuf_kernel(int64_t n, int count, double 
 #pragma clang fp contract(off)
   const int64_t step = (int64_t)gridDim.x * 256 * 4;
   for (int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; e < n; e += step) {
-    if (ALIGNED && e + 3 < n) {
+    if (e + 3 < n) {
+      const f32x4_t w4 = load4<STREAM>(wg + e), d4 = load4<STREAM>(delta + e);
       double s[4] = {0.0, 0.0, 0.0, 0.0};
-      for (int i = 0; i < count; ++i) {
-        const float4 m = *reinterpret_cast<const float4*>(models + (int64_t)i * stride + e);
-        s[0] = s[0] + (double)m.x;
-        s[1] = s[1] + (double)m.y;
-        s[2] = s[2] + (double)m.z;
-        s[3] = s[3] + (double)m.w;
+      const float* m = models + e;
+      int i = 0;
+      for (; i + 8 <= count; i += 8) add_models<8, STREAM>(s, m + (int64_t)i * stride, stride);
+      if (count - i >= 4) {
+        add_models<4, STREAM>(s, m + (int64_t)i * stride, stride);
+        i += 4;
       }
-      const float4 w4 = *reinterpret_cast<const float4*>(wg + e);
-      const float4 d4 = *reinterpret_cast<const float4*>(delta + e);
-      const BmufOne r0 = bmuf_one(s[0], w4.x, d4.x, workers, eta, eta_next, zeta);
-      const BmufOne r1 = bmuf_one(s[1], w4.y, d4.y, workers, eta, eta_next, zeta);
-      const BmufOne r2 = bmuf_one(s[2], w4.z, d4.z, workers, eta, eta_next, zeta);
-      const BmufOne r3 = bmuf_one(s[3], w4.w, d4.w, workers, eta, eta_next, zeta);
-      const float4 nw = make_float4(r0.w, r1.w, r2.w, r3.w);
-      *reinterpret_cast<float4*>(wg + e) = nw;
-      *reinterpret_cast<float4*>(delta + e) = make_float4(r0.d, r1.d, r2.d, r3.d);
-      if (local) *reinterpret_cast<float4*>(local + e) = nw;
+      for (; i < count; ++i) add_models<1, STREAM>(s, m + (int64_t)i * stride, stride);
+      f32x4_t nw, nd;
+      u16x4_t b;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const BmufOne r = bmuf_one(s[q], w4[q], d4[q], workers, eta, eta_next, zeta);
+        nw[q] = r.w;
+        nd[q] = r.d;
+        b[q] = f32_to_bf16(r.w);
+      }
+      store4<STREAM>(wg + e, nw);
+      store4<STREAM>(delta + e, nd);
+      if (local) store4<STREAM>(local + e, nw);
       if (local_bf16) {
-        uint2 b;
-        b.x = (uint32_t)f32_to_bf16(nw.x) | ((uint32_t)f32_to_bf16(nw.y) << 16);
-        b.y = (uint32_t)f32_to_bf16(nw.z) | ((uint32_t)f32_to_bf16(nw.w) << 16);
-        *reinterpret_cast<uint2*>(local_bf16 + e) = b;
+        if constexpr (STREAM) __builtin_nontemporal_store(b, reinterpret_cast<u16x4_u*>(local_bf16 + e));
+        else *reinterpret_cast<u16x4_u*>(local_bf16 + e) = b;
       }
     } else {
-      for (int64_t j = e; j < e + 4 && j < n; ++j) {
+      for (int64_t j = e; j < n; ++j) {
         double s = 0.0;
         for (int i = 0; i < count; ++i) s = s + (double)models[(int64_t)i * stride + j];
         const BmufOne r = bmuf_one(s, wg[j], delta[j], workers, eta, eta_next, zeta);
@@ -85,21 +125,17 @@ hipError_t bmuf_update(int64_t n, int count, int workers, const float* models, i
                        float* wg, float* delta, float eta, float eta_next, float zeta,
                        float* local, uint16_t* local_bf16, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const uintptr_t bits = reinterpret_cast<uintptr_t>(models) | reinterpret_cast<uintptr_t>(wg) |
-                         reinterpret_cast<uintptr_t>(delta) | reinterpret_cast<uintptr_t>(local);
-  const bool aligned = (bits & 15) == 0 && (reinterpret_cast<uintptr_t>(local_bf16) & 7) == 0 &&
-                       (count == 1 || stride % 4 == 0);
-  const int64_t quads = (n + 3) / 4;
-  const int64_t want = (quads + 255) / 256;
-  const unsigned blocks = (unsigned)(want < 8192 ? want : 8192);
-  if (aligned)
-    hipLaunchKernelGGL(bmuf_kernel<true>, dim3(blocks), dim3(256), 0, s, n, count, (double)workers,
-                       models, stride, wg, delta, (double)eta, (double)eta_next, (double)zeta,
-                       local, local_bf16);
-  else
-    hipLaunchKernelGGL(bmuf_kernel<false>, dim3(blocks), dim3(256), 0, s, n, count,
-                       (double)workers, models, stride, wg, delta, (double)eta, (double)eta_next,
-                       (double)zeta, local, local_bf16);
+  const int64_t want = ((n + 3) / 4 + 255) / 256;
+  const unsigned blocks = (unsigned)(want < (1 << 20) ? want : (1 << 20));
+  // Arrays that the 256 MB memory-side cache holds are left in it; larger ones
+  // only push one another out and are streamed past it.  24.1 M elements with 8
+  // addends (1.3 GB): 229 us streamed, 239 with cached stores; 6 M with 5 (250
+  // MB): 39.8 and 47; 3 M with 1 (78 MB): 14.9 and 12.7.
+  const int64_t bytes = n * (4 * (int64_t)count + 8 + 8 + (local ? 4 : 0) + (local_bf16 ? 2 : 0));
+  const bool stream = bytes > ((int64_t)128 << 20);
+  hipLaunchKernelGGL(stream ? bmuf_kernel<true> : bmuf_kernel<false>, dim3(blocks), dim3(256), 0, s, n, count,
+                     (double)workers, models, stride, wg, delta, (double)eta, (double)eta_next,
+                     (double)zeta, local, local_bf16);
   return hipGetLastError();
 }
 

@@ -139,6 +139,33 @@ def test_bmuf_bit_exact(n, N, count, outputs):
         np.testing.assert_array_equal(lb.cpu().view(torch.int16).numpy().view(np.uint16), ref_b)
 
 
+# every remainder of the batches of model loads (8, 4, 1), arrays that start
+# off the 16-byte grid, and sizes on both sides of the streaming line (128 MiB
+# touched: 38 bytes an element with 4 addends, 3,531,985 elements)
+@pytest.mark.parametrize("n,N", [(1023, c) for c in (1, 2, 5, 7, 8, 11, 12, 13, 16)] +
+                         [(3_531_985, 4), (3_531_987, 4), (3_600_002, 5)])
+def test_bmuf_batches_and_alignment(n, N):
+    say(f"bmuf n={n} N={N} offset views")
+    base, models, delta = _bmuf_case(n, N, seed=2)
+
+    def shifted(a, k=1, dtype=None):
+        t = torch.zeros(a.size + k, dtype=dtype or torch.float32, device="cuda")
+        t[k:] = to_dev(a.ravel())
+        return t, t[k:].view(a.shape)
+
+    (md0, md), (wg0, wg), (dd0, dd) = shifted(models), shifted(base, 3), shifted(delta, 2)
+    (lm0, lm) = shifted(np.zeros(n, np.float32))
+    (lb0, lb) = shifted(np.zeros(n, np.float32), 1, torch.bfloat16)
+    am.bmuf_block_update(md, N, wg, dd, 0.5, 0.75, 1.5, lm, lb)
+    torch.cuda.synchronize()
+    ref_w, ref_d, ref_b = oracle.bmuf_block_update(models, N, base, delta, 0.5, 0.75, 1.5)
+    for got, ref in ((wg, ref_w), (dd, ref_d), (lm, ref_w), (md, models)):
+        np.testing.assert_array_equal(_bits32(got.cpu().numpy()), _bits32(ref))
+    np.testing.assert_array_equal(lb.cpu().view(torch.int16).numpy().view(np.uint16), ref_b)
+    for whole, k in ((md0, 1), (wg0, 3), (dd0, 2), (lm0, 1), (lb0, 1)):
+        assert not whole[:k].any()
+
+
 def test_bmuf_unaligned_and_aliased_restart_copy():
     # offset views (not 16-byte aligned) and the restart copy written over
     # the first addend
