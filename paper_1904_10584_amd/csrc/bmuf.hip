@@ -67,7 +67,7 @@ __device__ __forceinline__ void add_models(double* s, const float* m, int64_t st
 // Four elements a thread, the whole array in one grid (8192 workgroups in a
 // loop ended unevenly: 258 us below).  What bounds it: HBM.  STREAM: every
 // access non-temporal (see the launch).  24,145,848 elements, 8 addends, both
-// restart copies (1.30 GB): 247 -> 229 us; 10,000,001 elements, 3 addends, whose
+// restart copies (1.30 GB): 245 -> 216 us; 10,000,001 elements, 3 addends, whose
 // rows start off the 16-byte grid (one element at a time before): 216 -> 59.
 template <bool STREAM>
 __global__ __launch_bounds__(256) void bmuf_kernel(int64_t n, int count, double workers,
@@ -129,7 +129,7 @@ hipError_t bmuf_update(int64_t n, int count, int workers, const float* models, i
   const unsigned blocks = (unsigned)(want < (1 << 20) ? want : (1 << 20));
   // Arrays that the 256 MB memory-side cache holds are left in it; larger ones
   // only push one another out and are streamed past it.  24.1 M elements with 8
-  // addends (1.3 GB): 229 us streamed, 239 with cached stores; 6 M with 5 (250
+  // addends (1.3 GB): 233 us with fp32 stores streamed, 238 with loads cached; 6 M with 5 (250
   // MB): 39.8 and 47; 3 M with 1 (78 MB): 14.9 and 12.7.
   const int64_t bytes = n * (4 * (int64_t)count + 8 + 8 + (local ? 4 : 0) + (local_bf16 ? 2 : 0));
   const bool stream = bytes > ((int64_t)128 << 20);
