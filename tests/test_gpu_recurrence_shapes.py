@@ -148,3 +148,26 @@ def test_layers_in_one_launch_run_repeatedly(layers, hidden, B, T, fenced, monke
     for k in ("logits", "grads"):
         a, b = first[k].astype(np.float64), one[k].astype(np.float64)
         assert np.linalg.norm(a - b) <= 1e-2 * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("layers,hidden,B,T,varlen", [
+    (5, 768, 12, 32, False), (4, 704, 32, 20, True), (3, 640, 20, 20, False), (2, 576, 16, 9, False),
+    (3, 512, 48, 40, True), (2, 448, 60, 20, False), (3, 384, 70, 20, True), (2, 320, 16, 20, False),
+    (5, 256, 40, 30, False), (3, 192, 33, 12, True), (8, 128, 32, 9, False)])
+def test_layers_in_one_launch_give_the_bits_of_layer_after_layer(layers, hidden, B, T, varlen, monkeypatch):
+    # each launch's shape: the layers above the first get the same projections
+    # to the last bit, whichever kernel makes them
+    dims = oracle.ModelDims(layers, 40, hidden, 72)
+    lengths = None
+    if varlen:
+        lengths = np.sort(np.random.default_rng(hidden + B).integers(0, T + 1, B))[::-1].astype(np.int32)
+        lengths[0] = T
+    m = am.Model(dims.layers, dims.input_dim, dims.hidden, dims.classes, am.BF16)
+    say(f"one launch against layer after layer L={layers} H={hidden} B={B} T={T} varlen={varlen}")
+    master, x, idx, prob, h0, c0 = _problem(dims, T, B, 6, 0.98, lengths, seed=61, state=True)
+    got = gpu_forward_backward(m, master, x, T, B, idx, prob, lengths, h0, c0, want_state=True)
+    monkeypatch.setenv("AM_RECURRENCE", "xcd")
+    ref = gpu_forward_backward(m, master, x, T, B, idx, prob, lengths, h0, c0, want_state=True)
+    for k in ref:
+        np.testing.assert_array_equal(np.asarray(got[k]).view(np.uint32) if k != "loss" else got[k],
+                                      np.asarray(ref[k]).view(np.uint32) if k != "loss" else ref[k])
