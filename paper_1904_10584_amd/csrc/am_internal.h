@@ -240,7 +240,8 @@ struct LfrArgs {
   const float* std;    // [stack * raw_dim]
   void* x;             // packed [N][stack * raw_dim], model dtype
 };
-hipError_t lfr_features(const LfrArgs& a, bool bf16, hipStream_t s);
+// (longest, frames: the most stacked frames of an utterance, and all of them)
+hipError_t lfr_features(const LfrArgs& a, int longest, int64_t frames, bool bf16, hipStream_t s);
 // Targets of packed rows delayed by `delay` frames within each sequence.
 struct DelayArgs {
   int T, B, K, delay;

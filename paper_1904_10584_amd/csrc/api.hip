@@ -813,13 +813,14 @@ am_status lfr_features(int32_t B, const int32_t* raw_lengths, const float* raw, 
   memset(&a, 0, sizeof a);
   a.B = B; a.raw_dim = raw_dim; a.stack = stack; a.skip = skip; a.offset = offset;
   int64_t frames = 0, raws = 0;
-  int32_t prev = 0;
+  int32_t prev = 0, longest = 0;
   for (int b = 0; b < B; ++b) {
     if (raw_lengths[b] < 0 || raw_lengths[b] > 65535)
       return fail(AM_EUNSUPPORTED, "raw_lengths[%d] = %d outside [0, 65535]", b, raw_lengths[b]);
     const int32_t T = am_lfr_frames(raw_lengths[b], stack, skip, offset);
     if (b > 0 && T > prev)
       return fail(AM_EINVAL, "stacked lengths must be non-increasing (utterance %d)", b);
+    if (b == 0) longest = T;
     prev = T;
     frames += T;
     raws += raw_lengths[b];
@@ -831,7 +832,7 @@ am_status lfr_features(int32_t B, const int32_t* raw_lengths, const float* raw, 
   hipStream_t s = static_cast<hipStream_t>(stream);
   const double bytes = (double)frames * stack * raw_dim * (4 + (x_dtype == AM_BF16 ? 2 : 4));
   Timed tm(AM_K_MISC, s, 0.0, bytes);
-  return hip_check(am::lfr_features(a, x_dtype == AM_BF16, s), "lfr_features");
+  return hip_check(am::lfr_features(a, longest, frames, x_dtype == AM_BF16, s), "lfr_features");
 }
 
 am_status delay_targets(int32_t T, int32_t B, const int32_t* lengths, int32_t K, int32_t delay,

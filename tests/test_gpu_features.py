@@ -96,6 +96,44 @@ def test_lfr_features_chunk_edges_and_special_values(raw_dim):
     np.testing.assert_array_equal(got.view(np.uint32)[ok], ref.view(np.uint32)[ok])
 
 
+# many short utterances, which one workgroup each walks: fewer frames than are
+# loaded ahead (32), one more, several times as many; one pass of 256 dimensions,
+# a remainder, two passes; ended and empty sequences
+@pytest.mark.parametrize("B,T,raw_dim,ragged,bf16", [(300, 20, 40, True, True), (1000, 9, 80, True, False),
+                                                     (1000, 33, 21, True, True), (350, 66, 80, False, False),
+                                                     (300, 12, 100, True, True), (1000, 100, 80, False, True)])
+def test_lfr_features_many_short_utterances(B, T, raw_dim, ragged, bf16):
+    rng = np.random.default_rng(B + T)
+    lens = np.sort(rng.integers(0, T + 1, B))[::-1].astype(np.int32) if ragged else np.full(B, T, np.int32)
+    lens[0] = T
+    U = np.maximum(3 * lens + np.arange(B, dtype=np.int32) % 3, 0).astype(np.int32)
+    D = 3 * raw_dim
+    raw = rng.normal(2.0, 3.0, (int(U.sum()), raw_dim)).astype(np.float32)
+    raw.reshape(-1)[rng.integers(0, raw.size, 20)] = np.float32(np.inf)
+    mean = rng.normal(0, 0.5, D).astype(np.float32)
+    std = rng.uniform(0.5, 2.0, D).astype(np.float32)
+    _, offs = oracle.batch_schedule(T, B, lens)
+    ref = np.zeros((int(offs[-1]), D), np.float32)
+    r0 = 0
+    with np.errstate(all="ignore"):
+        for b in range(B):
+            n = int(lens[b])
+            y = raw[r0:r0 + 3 * n].reshape(n, D).astype(np.float64)
+            run = np.cumsum(y, axis=0)  # (frame by frame, as the definition's sum)
+            z = y - run / np.arange(1, n + 1, dtype=np.float64)[:, None]
+            ref[offs[:n].astype(int) + b] = ((z - mean.astype(np.float64)) / std.astype(np.float64)).astype(np.float32)
+            r0 += int(U[b])
+    say(f"lfr features, short utterances: B={B} T={T} D={D} ragged={ragged} bf16={bf16}")
+    x = torch.zeros(ref.shape, dtype=torch.bfloat16 if bf16 else torch.float32, device="cuda")
+    am.lfr_features(U, to_dev(raw), to_dev(mean), to_dev(std), x)
+    got = x.float().cpu().numpy()
+    if bf16:
+        ref = np.where(np.isnan(ref), ref, (oracle.bf16_bits(ref).astype(np.uint32) << 16).view(np.float32))
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+    ok = ~np.isnan(ref)
+    np.testing.assert_array_equal(got.view(np.uint32)[ok], ref.view(np.uint32)[ok])
+
+
 @pytest.mark.parametrize("lengths_kind", [None, "varlen"])
 @pytest.mark.parametrize("delay", [0, 1, 3])
 def test_delay_targets_bit_exact(lengths_kind, delay):
