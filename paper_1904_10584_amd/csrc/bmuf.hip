@@ -64,11 +64,12 @@ __device__ __forceinline__ void add_models(double* s, const float* m, int64_t st
     for (int q = 0; q < 4; ++q) s[q] = s[q] + (double)v[k][q];
 }
 
-// Four elements a thread, the whole array in one grid (8192 workgroups in a
-// loop ended unevenly: 258 us below).  What bounds it: HBM.  STREAM: every
-// access non-temporal (see the launch).  24,145,848 elements, 8 addends, both
-// restart copies (1.30 GB): 245 -> 216 us; 10,000,001 elements, 3 addends, whose
-// rows start off the 16-byte grid (one element at a time before): 216 -> 59.
+// Four elements a thread, the whole array in one grid (a loop over 8192
+// workgroups ended unevenly: 258 us where one grid took 239).  What bounds it:
+// HBM.  STREAM: every access non-temporal (see the launch).  24,145,848
+// elements, 8 addends, both restart copies (1.30 GB): 245 -> 216 us on one card,
+// 248 -> 229 on another; 10,000,001 elements, 3 addends, whose rows start off
+// the 16-byte grid (one element at a time before): 216 -> 59.
 template <bool STREAM>
 __global__ __launch_bounds__(256) void bmuf_kernel(int64_t n, int count, double workers,
                                                    const float* models,
@@ -127,12 +128,17 @@ hipError_t bmuf_update(int64_t n, int count, int workers, const float* models, i
   if (n <= 0) return hipSuccess;
   const int64_t want = ((n + 3) / 4 + 255) / 256;
   const unsigned blocks = (unsigned)(want < (1 << 20) ? want : (1 << 20));
-  // Arrays that the 256 MB memory-side cache holds are left in it; larger ones
-  // only push one another out and are streamed past it.  24.1 M elements with 8
-  // addends (1.3 GB): 233 us with fp32 stores streamed, 238 with loads cached; 6 M with 5 (250
-  // MB): 39.8 and 47; 3 M with 1 (78 MB): 14.9 and 12.7.
-  const int64_t bytes = n * (4 * (int64_t)count + 8 + 8 + (local ? 4 : 0) + (local_bf16 ? 2 : 0));
-  const bool stream = bytes > ((int64_t)128 << 20);
+  // Streamed where the 256 MB memory-side cache keeps nothing from one update to
+  // the next: the addends alone overflow it, or everything touched does twice
+  // over.  Below, what is left in it (the models were just written, and the last
+  // update's results) is worth more.  Plain / streamed, us, models just written:
+  // 8 M x 3 (259 MiB) 43.4 / 44.4, 10 M x 4 (362 MiB) 58.6 / 59.7, 20 M x 1 (496
+  // MiB) 83.6 / 84.2, 10 M x 8 (addends 305 MiB) 97.4 / 90.5, 20 M x 2 (572 MiB)
+  // 104 / 96, 24.1 M x 8 (1.2 GiB) 246 / 218; updates back to back: 40.1 / 45.5,
+  // 56.1 / 62.3, 79.3 / 87.9, 94.3 / 88.4, 105.8 / 104.4 and 247 / 221.
+  const int64_t addends = n * 4 * (int64_t)count;
+  const int64_t bytes = addends + n * (8 + 8 + (local ? 4 : 0) + (local_bf16 ? 2 : 0));
+  const bool stream = addends > ((int64_t)256 << 20) || bytes > ((int64_t)544 << 20);
   hipLaunchKernelGGL(stream ? bmuf_kernel<true> : bmuf_kernel<false>, dim3(blocks), dim3(256), 0, s, n, count,
                      (double)workers, models, stride, wg, delta, (double)eta, (double)eta_next,
                      (double)zeta, local, local_bf16);

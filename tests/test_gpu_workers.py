@@ -140,10 +140,12 @@ def test_bmuf_bit_exact(n, N, count, outputs):
 
 
 # every remainder of the batches of model loads (8, 4, 1), arrays that start
-# off the 16-byte grid, and sizes on both sides of the streaming line (128 MiB
-# touched: 38 bytes an element with 4 addends, 3,531,985 elements)
+# off the 16-byte grid, larger arrays, and sizes on both sides of the streaming
+# lines (256 MiB of addends: 16 of 4,194,304 elements; 544 MiB touched: one
+# addend, 26 bytes an element, 21,940,066 elements)
 @pytest.mark.parametrize("n,N", [(1023, c) for c in (1, 2, 5, 7, 8, 11, 12, 13, 16)] +
-                         [(3_531_985, 4), (3_531_987, 4), (3_600_002, 5)])
+                         [(3_531_985, 4), (3_531_987, 4), (3_600_002, 5),
+                          (4_194_303, 16), (4_194_307, 16), (21_940_069, 1)])
 def test_bmuf_batches_and_alignment(n, N):
     say(f"bmuf n={n} N={N} offset views")
     base, models, delta = _bmuf_case(n, N, seed=2)
