@@ -91,8 +91,10 @@ hipError_t lstm_cell_fwd(const float* pre, const LstmFwdStep& a, hipStream_t s);
 hipError_t lstm_cell_bwd(const float* dhrec, int splits, const LstmBwdStep& a, hipStream_t s);
 
 // A bf16 backward step in one launch, product and cell (reads WhT, not Wh):
-// shapes whose tiles fill at least half of the chip (see lstm_bstep.hip).
+// shapes whose tiles fill at least half of the chip and at most all of it, and
+// whether `steps` of them pay for the transpose (see lstm_bstep.hip).
 bool lstm_bwd_step_fused_covers(int hidden, int nb);
+bool lstm_bwd_fused_pays(int hidden, int steps);
 hipError_t lstm_bwd_step_fused_launch(const LstmBwdStep& a, hipStream_t s);
 
 // Persistent layer kernels (all time steps in one launch of a resident grid).

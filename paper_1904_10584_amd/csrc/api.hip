@@ -1174,6 +1174,9 @@ am_status lstm_am_backward(const am_model* m, const void* params, const void* x,
   float* dc = at<float>(ws, w.dc);
   // the XCD-local recurrences read W_h^T: every layer's, transposed up front
   // in one launch (falls back to one transpose per layer below)
+  int fused_steps = 0;  // steps that the one-launch step would take
+  for (int t = 0; t < T; ++t)
+    fused_steps += am::lstm_bwd_step_fused_covers((int)H, (int)sc.counts[t]);
   bool wht_ready = false;
   if (sc.N > 0 && xcd_path(bf, H, sc) && !solo_shape(bf, H, T, B, is_varlen(sc))) {
     Timed tm(AM_K_MISC, s, 0.0, 2.0 * L * G * H * e);
@@ -1234,8 +1237,7 @@ am_status lstm_am_backward(const am_model* m, const void* params, const void* x,
       }
     }
     // (per step in bf16: the fused step reads W_h^T, the split product W_h)
-    const bool fused = !used && bf && sc.N > 0 &&
-                       am::lstm_bwd_step_fused_covers((int)H, (int)sc.counts[0]);
+    const bool fused = !used && bf && am::lstm_bwd_fused_pays((int)H, fused_steps);
     if (!used && (!bf || fused)) {
       Timed tm(AM_K_MISC, s, 0.0, 2.0 * G * H * e);
       AM_TRY(hip_check(am::transpose(P8 + po.wh[l] * e, WhT, (int)G, (int)H, bf, s), "Wh transpose"));

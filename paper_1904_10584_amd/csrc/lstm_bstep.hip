@@ -182,9 +182,27 @@ __global__ __launch_bounds__(THREADS, 1) void lstm_bwd_step_fused(LstmBwdStep a,
 
 }  // namespace
 
+// Which steps: a workgroup fills a compute unit, so up to 256 tiles, one round
+// (backward of one layer, split product and cell / fused: 1536 cells, 9 steps of
+// 512 sequences, 256 tiles, 379 / 363 us; 576 sequences, 288 tiles, 415 / 521;
+// 2048 cells x 384, 258 tiles, 444 / 601), and at least 128: half of the chip
+// (1536 cells x 256, 128 tiles, 301 / 286; fewer also gain 2-10 % but are not
+// taken).  Beyond 2048 cells the longer k-loop reads the operands no faster than
+// the split product does (2560 cells x 256, 64 steps 3247 / 3285; 3072 x 256 4295 /
+// 4480).
 bool lstm_bwd_step_fused_covers(int hidden, int nb) {
   const int tiles = ((nb + TM - 1) / TM) * ((hidden + TU - 1) / TU);
-  return hidden % 32 == 0 && tiles >= 128;
+  return hidden % 32 == 0 && hidden <= 2048 && tiles >= 128 && tiles <= 256;
+}
+
+// Whether so many of them are worth W_h's transpose, which the split product
+// does without: the transpose takes as long as 0.3 (512 cells), 2.3 (1536) to 4
+// steps (2048) gain, and the last step has no product.  Split / fused at 1, 2, 3,
+// 4, 6 steps, us: 768 cells x 1024 sequences 70 / 75, 101 / 100, 130 / 124, 158 /
+// 148, 219 / 204; 1536 x 256 54 / 61, 88 / 94, 124 / 126, 149 / 149, 207 / 201; 2048
+// x 256 64 / 76, 107 / 117, 149 / 156, 182 / 187, 256 / 256.
+bool lstm_bwd_fused_pays(int hidden, int steps) {
+  return (int64_t)(steps - 2) * (1 << 20) >= (int64_t)hidden * hidden;
 }
 
 hipError_t lstm_bwd_step_fused_launch(const LstmBwdStep& a, hipStream_t s) {
