@@ -298,7 +298,7 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
   };
   int nb = active_down(ps, ps.B, 0), off = 0, off_prev = 0, nb_prev = 0;
   load_pin(0, 0, nb);
-  unsigned spins = 0;
+  PollBudget<SPIN_LIMIT> polls;
   // every load so far (weights, state, the first projections) is complete
   // here, so the compiler keeps no waits for them inside the loop
   wait_vm<0>();
@@ -335,6 +335,7 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
           const bf16_t* hs = hring + ((t - 1) & (RING_SLOTS - 1)) * slot;
           const uint32_t at = (uint32_t)(min(b0 + r, nb - 1) * H + l0 * 64 + (lane & 7) * 8);
           u32x4_t v[PQ];
+          polls.begin();
           for (;;) {
 #pragma unroll
             for (int i = 0; i < PQ; ++i)
@@ -347,7 +348,7 @@ __global__ __launch_bounds__(512, 1) void lstm_fwd_xcd(PersistFwd a, PersistSche
               for (int k = 0; k < 4; ++k)
                 top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2_t, (uint32_t)v[i][k]));
             if (!__any(top[0] == 0xffffu || top[1] == 0xffffu)) break;
-            if (++spins > SPIN_LIMIT) {  // (over all steps: after a time-out none waits again)
+            if (polls.spent()) {
               if (lane == 0) __hip_atomic_store(y.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               break;
             }

@@ -5,6 +5,7 @@
 
 #include "am_device.h"
 #include "am_internal.h"
+#include "poll_budget.h"
 
 namespace am {
 namespace {
