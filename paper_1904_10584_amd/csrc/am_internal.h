@@ -99,7 +99,8 @@ hipError_t lstm_bwd_step_fused_launch(const LstmBwdStep& a, hipStream_t s);
 
 // Persistent layer kernels (all time steps in one launch of a resident grid).
 // The schedule of a batch: T steps, B sequences, N frames; with varlen the
-// sorted lengths (B <= 1024), else every sequence has T frames.
+// sorted lengths (B <= 1024; the XCD-local kernels' launchers may put the steps'
+// active sequences there instead), else every sequence has T frames.
 struct PersistSchedule {
   int T, B, N;
   int first;  // first sequence of this launch (XCD-local kernels: a round of the batch)

@@ -119,12 +119,19 @@ __device__ __forceinline__ int xcd_block(int members) {
   return (int)(blockIdx.x % NX) + NX * (int)(blockIdx.x / NX / members);
 }
 
+// Sequences longer than t steps, from those at t - 1 (active_down) or t + 1
+// (active_up), walked through the sorted lengths one load after another; or,
+// COUNTS, read from ps.lens[t].
+template <bool COUNTS = false>
 __device__ __forceinline__ int active_down(const PersistSchedule& ps, int nb, int t) {
+  if constexpr (COUNTS) return ps.lens[t];
   if (!ps.varlen) return ps.B;
   while (nb > 0 && (int)ps.lens[nb - 1] <= t) --nb;
   return nb;
 }
+template <bool COUNTS = false>
 __device__ __forceinline__ int active_up(const PersistSchedule& ps, int nb, int t) {
+  if constexpr (COUNTS) return ps.lens[t];
   if (!ps.varlen) return ps.B;
   while (nb < ps.B && (int)ps.lens[nb] > t) ++nb;
   return nb;

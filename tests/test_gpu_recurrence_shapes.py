@@ -171,3 +171,22 @@ def test_layers_in_one_launch_give_the_bits_of_layer_after_layer(layers, hidden,
     for k in ref:
         np.testing.assert_array_equal(np.asarray(got[k]).view(np.uint32) if k != "loss" else got[k],
                                       np.asarray(ref[k]).view(np.uint32) if k != "loss" else ref[k])
+
+
+@pytest.mark.parametrize("hidden,B,longest", [(192, 9, 40), (320, 150, 900), (768, 128, 25), (256, 1000, 30),
+                                              (1024, 300, 13), (384, 492, 8)])
+def test_active_sequences_read_or_walked(hidden, B, longest, monkeypatch):
+    # up to 1024 steps the kernels read each step's active sequences, beyond they
+    # walk the sorted lengths; T beyond the longest sequence changes nothing else
+    monkeypatch.setenv("AM_RECURRENCE", "xcd")
+    dims = oracle.ModelDims(1, 24, hidden, 40)
+    lengths = np.sort(np.random.default_rng(hidden + B).integers(0, longest + 1, B))[::-1].astype(np.int32)
+    lengths[0] = longest
+    m = am.Model(dims.layers, dims.input_dim, dims.hidden, dims.classes, am.BF16)
+    say(f"active sequences H={hidden} B={B} longest={longest}")
+    assert all(am.recurrence_path(m, T, B, True) == am.PATH_XCD for T in (longest, 1100))
+    master, x, idx, prob, h0, c0 = _problem(dims, longest, B, 6, 0.98, lengths, seed=67, state=True)
+    got = gpu_forward_backward(m, master, x, longest, B, idx, prob, lengths, h0, c0, want_state=True)
+    ref = gpu_forward_backward(m, master, x, 1100, B, idx, prob, lengths, h0, c0, want_state=True)
+    for k in ref:
+        np.testing.assert_array_equal(np.asarray(got[k]), np.asarray(ref[k]))
