@@ -94,22 +94,27 @@ int64_t am_encode_workspace_bytes(int64_t n);
 const char* am_status_string(int32_t status);
 const char* am_last_error(void);
 
-/* Which kernels run one layer's recurrence (forward = 1: the forward pass;
- * 0: BPTT) for a batch of B sequences and T steps (varlen = 1 if their
- * lengths differ), as lstm_am_forward / lstm_am_backward choose them:
+/* Which kernels run the recurrence (forward = 1: the forward pass; 0: BPTT)
+ * for a batch of B sequences and T steps (varlen = 1 if their lengths differ),
+ * as lstm_am_forward / lstm_am_backward choose them:
  *   AM_PATH_SOLO   one launch per layer, each workgroup running 16 sequences
  *                  through every step by itself (narrow layers; variable
  *                  lengths need T <= 65535);
- *   AM_PATH_XCD    one persistent launch per layer whose blocks of sequences
- *                  each exchange state inside one XCD's L2 (bf16, shapes the
- *                  kernels are built for; variable lengths need T <= 65535);
+ *   AM_PATH_PIPE   one persistent launch for all layers of a forward pass, the
+ *                  layers a few steps behind one another (bf16, few sequences
+ *                  for the number of layers; variable lengths need T <= 65535);
+ *   AM_PATH_XCD    one persistent launch per layer (several where the sequences
+ *                  go in rounds) whose blocks of sequences each exchange state
+ *                  inside one XCD's L2 (bf16, shapes the kernels are built
+ *                  for; variable lengths need T <= 65535);
  *   AM_PATH_DEVICE one persistent launch per layer with a device-scope
  *                  exchange (its grid checked against the current device's
  *                  occupancy: never chosen without a device);
  *   AM_PATH_STEP   one launch per time step.
- * A persistent grid that cannot be resident at launch falls back to the
- * next path.  -1 if the model or sizes are invalid.  Host only. */
-enum { AM_PATH_XCD = 1, AM_PATH_DEVICE = 2, AM_PATH_STEP = 3, AM_PATH_SOLO = 4 };
+ * blstm_teacher_forward runs its layers one after another: AM_PATH_PIPE there
+ * means AM_PATH_XCD.  A persistent grid that cannot be resident at launch falls
+ * back to the next path.  -1 if the model or sizes are invalid.  Host only. */
+enum { AM_PATH_XCD = 1, AM_PATH_DEVICE = 2, AM_PATH_STEP = 3, AM_PATH_SOLO = 4, AM_PATH_PIPE = 5 };
 int32_t am_recurrence_path(const am_model* m, int32_t T, int32_t B, int32_t varlen,
                            int32_t forward);
 

@@ -25,7 +25,7 @@ KERNEL_CLASSES = ["gemm_fwd", "gemm_bwd_data", "gemm_bwd_wgt", "lstm_fwd", "lstm
 
 
 OK, EINVAL, ECAPACITY, EUNSUPPORTED, EHIP, EWORKSPACE, ETIMEOUT = 0, -1, -2, -3, -4, -5, -6
-PATH_XCD, PATH_DEVICE, PATH_STEP, PATH_SOLO = 1, 2, 3, 4
+PATH_XCD, PATH_DEVICE, PATH_STEP, PATH_SOLO, PATH_PIPE = 1, 2, 3, 4, 5
 
 
 class AmError(RuntimeError):
@@ -174,8 +174,8 @@ def workspace_bytes(m: Model, T, B, N) -> int:
 
 
 def recurrence_path(m: Model, T, B, varlen=False, forward=True) -> int:
-    """PATH_SOLO, PATH_XCD, PATH_DEVICE or PATH_STEP: the kernels a layer's recurrence
-    takes for this batch shape (see am_recurrence_path)."""
+    """PATH_SOLO, PATH_PIPE, PATH_XCD, PATH_DEVICE or PATH_STEP: the kernels the
+    recurrence takes for this batch shape (see am_recurrence_path)."""
     p = lib().am_recurrence_path(ctypes.byref(m.c()), T, B, 1 if varlen else 0, 1 if forward else 0)
     if p < 0:
         raise AmError("invalid model or batch for the recurrence-path query", EINVAL)

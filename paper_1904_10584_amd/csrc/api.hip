@@ -278,11 +278,11 @@ bool solo_shape(bool bf, int64_t H, int T, int B, bool varlen) {
 // Whether the forward pass runs every layer in one launch: where the XCD-local
 // kernels would run them one after another (and no environment variable asks
 // for one path) and the layers' blocks of sequences have room side by side.
-bool pipe_path(bool bf, int64_t H, int64_t L, const Schedule& sc) {
+bool pipe_shape(bool bf, int64_t H, int64_t L, int T, int B, bool varlen) {
   const char* r = getenv("AM_RECURRENCE");
   const char* o = getenv("AM_XCD_BLOCKS");
-  return !(r && r[0]) && !(o && o[0] == '1') && xcd_path(bf, H, sc) &&
-         !solo_shape(bf, H, sc.T, sc.B, is_varlen(sc)) && am::lstm_pipe_covers((int)H, sc.B, (int)L);
+  return !(r && r[0]) && !(o && o[0] == '1') && xcd_shape(bf, H, T, B, varlen) &&
+         !solo_shape(bf, H, T, B, varlen) && am::lstm_pipe_covers((int)H, B, (int)L);
 }
 
 // AM_DEBUG=1 in the environment: entry points that consume indices held in
@@ -376,8 +376,9 @@ am::GemmArgs mk_gemm(const void* A, int64_t lda, bool ak, const void* B, int64_t
 }
 
 // One layer's recurrence, forward in time, over the packed rows of a
-// schedule: the XCD-local persistent kernel where it covers the shape, else
-// the device-scope persistent kernel, else one launch per time step.
+// schedule: narrow layers by a workgroup per 16 sequences, else the XCD-local
+// persistent kernel where it covers the shape, else the device-scope persistent
+// kernel, else one launch per time step.
 struct FwdLayer {
   const void* P;      // [N][4H] input projections + bias
   const void* Wh;     // [4H][H]
@@ -656,6 +657,7 @@ int32_t am_recurrence_path(const am_model* m, int32_t T, int32_t B, int32_t varl
   const bool bf = m->dtype == AM_BF16, fw = forward != 0;
   if (!persistent_enabled()) return AM_PATH_STEP;
   if (solo_shape(bf, m->hidden, T, B, varlen != 0)) return AM_PATH_SOLO;
+  if (fw && pipe_shape(bf, m->hidden, m->layers, T, B, varlen != 0)) return AM_PATH_PIPE;
   if (xcd_shape(bf, m->hidden, T, B, varlen != 0)) return AM_PATH_XCD;
   if (device_persistent_enabled() && am::lstm_persistent_fits(fw, m->hidden, B, bf, T))
     return AM_PATH_DEVICE;
@@ -1052,7 +1054,7 @@ am_status lstm_am_forward(const am_model* m, const void* params, const void* x,
   }
 
   // few sequences: every layer in one launch behind the first projection
-  const bool pipe = sc.N > 0 && pipe_path(bf, H, L, sc);
+  const bool pipe = sc.N > 0 && pipe_shape(bf, H, L, T, B, is_varlen(sc));
   bool piped = false;
   for (int l = 0; l < L && !piped; ++l) {
     const int64_t D = l == 0 ? m->input_dim : H;

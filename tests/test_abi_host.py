@@ -235,3 +235,21 @@ def test_profile_sampling_interval(L):
     assert L.am_profile_sample_every(-3) == am.EINVAL
     assert L.am_profile_sample_every(7) == am.OK
     assert L.am_profile_sample_every(1) == am.OK
+
+
+def test_recurrence_path_query_all_layers_in_one_launch(monkeypatch):
+    # a few sequences for the number of layers: the forward pass only, unless a
+    # path is asked for
+    for k in ("AM_STEP_KERNELS", "AM_XCD_FENCED", "AM_RECURRENCE", "AM_XCD_BLOCKS"):
+        monkeypatch.delenv(k, raising=False)
+    paper = am.Model(5, 192, 768, 3000, am.BF16)
+    assert am.recurrence_path(paper, 32, 12) == am.PATH_PIPE
+    assert am.recurrence_path(paper, 32, 12, True) == am.PATH_PIPE
+    assert am.recurrence_path(paper, 32, 12, False, False) == am.PATH_XCD
+    assert am.recurrence_path(paper, 32, 17) == am.PATH_XCD  # 10 slots, an XCD each
+    assert am.recurrence_path(paper, 65536, 12, True) not in (am.PATH_PIPE, am.PATH_XCD)
+    assert am.recurrence_path(am.Model(3, 120, 512, 2000, am.BF16), 40, 48) == am.PATH_PIPE
+    assert am.recurrence_path(am.Model(1, 120, 512, 2000, am.BF16), 40, 48) == am.PATH_XCD
+    assert am.recurrence_path(am.Model(3, 120, 512, 2000, am.F32), 40, 48) != am.PATH_PIPE
+    monkeypatch.setenv("AM_RECURRENCE", "xcd")
+    assert am.recurrence_path(paper, 32, 12) == am.PATH_XCD

@@ -126,6 +126,28 @@ def test_layers_in_one_launch(layers, hidden, B, T, varlen):
     _check(got, ref, dims, BF16_TOL, state=True)
 
 
+# the same shapes: the query says so, and the pass is one launch (the last one's
+# is one a layer)
+@pytest.mark.parametrize("layers,hidden,B,T", [
+    (2, 128, 20, 9), (8, 128, 32, 4), (3, 192, 33, 5), (4, 256, 17, 6), (2, 256, 128, 5), (2, 320, 16, 7),
+    (5, 320, 48, 4), (3, 384, 16, 5), (3, 384, 70, 5), (2, 448, 60, 4), (3, 448, 80, 4), (4, 512, 32, 5),
+    (3, 512, 48, 11), (2, 576, 16, 5), (3, 640, 20, 5), (4, 704, 32, 4), (5, 768, 12, 9), (8, 768, 1, 3),
+    (2, 768, 3, 1), (5, 512, 64, 3)])
+def test_layers_in_one_launch_taken(layers, hidden, B, T):
+    piped = (layers, hidden, B) != (5, 512, 64)
+    m = am.Model(layers, 40, hidden, 72, am.BF16)
+    say(f"layers in one launch, launches L={layers} H={hidden} B={B} T={T}")
+    assert am.recurrence_path(m, T, B) == (am.PATH_PIPE if piped else am.PATH_XCD)
+    assert am.recurrence_path(m, T, B, False, False) == am.PATH_XCD
+    master, x, idx, prob, _, _ = _problem(oracle.ModelDims(layers, 40, hidden, 72), T, B, 6, 0.98, seed=43)
+    am.profile_begin([am.KERNEL_CLASSES.index("lstm_fwd")])
+    try:
+        gpu_forward_backward(m, master, x, T, B, idx, prob)
+    finally:
+        am.profile_end()
+    assert am.profile_get(am.KERNEL_CLASSES.index("lstm_fwd"))["launches"] == (1 if piped else layers)
+
+
 @pytest.mark.parametrize("layers,hidden,B,T,fenced", [(5, 768, 12, 150, False), (3, 512, 48, 150, False),
                                                       (5, 256, 40, 150, False), (4, 384, 30, 40, True)])
 def test_layers_in_one_launch_run_repeatedly(layers, hidden, B, T, fenced, monkeypatch):
@@ -164,6 +186,7 @@ def test_layers_in_one_launch_give_the_bits_of_layer_after_layer(layers, hidden,
         lengths[0] = T
     m = am.Model(dims.layers, dims.input_dim, dims.hidden, dims.classes, am.BF16)
     say(f"one launch against layer after layer L={layers} H={hidden} B={B} T={T} varlen={varlen}")
+    assert am.recurrence_path(m, T, B, varlen) == am.PATH_PIPE
     master, x, idx, prob, h0, c0 = _problem(dims, T, B, 6, 0.98, lengths, seed=61, state=True)
     got = gpu_forward_backward(m, master, x, T, B, idx, prob, lengths, h0, c0, want_state=True)
     monkeypatch.setenv("AM_RECURRENCE", "xcd")
