@@ -42,6 +42,32 @@ def test_bf16_recurrence_shapes(hidden, B):
     _check(got, ref, dims, BF16_TOL, state=True)
 
 
+# the same on the XCD-local kernels alone, one layer after another (few sequences
+# would go through all layers in one launch, 64 cells through the solo kernels)
+@pytest.mark.parametrize("hidden,B", SHAPES + [(128, 33), (256, 270), (448, 128), (640, 128), (704, 128)])
+def test_bf16_recurrence_shapes_layer_after_layer(hidden, B, monkeypatch):
+    monkeypatch.setenv("AM_RECURRENCE", "xcd")
+    dims = oracle.ModelDims(2, 40, hidden, 72)
+    rounds = -(-B // (256 if hidden <= 768 else 128))
+    T = 5 if rounds == 1 else 4 * rounds + 1
+    lengths = np.sort(np.random.default_rng(hidden + B).integers(0, T + 1, B))[::-1].astype(np.int32)
+    lengths[0] = T
+    m = am.Model(dims.layers, dims.input_dim, dims.hidden, dims.classes, am.BF16)
+    say(f"recurrence shape, layer after layer H={hidden} B={B} T={T}")
+    for fwd in (True, False):
+        assert am.recurrence_path(m, T, B, True, fwd) == am.PATH_XCD
+    master, x, idx, prob, h0, c0 = _problem(dims, T, B, 6, 0.98, lengths, seed=23, state=True)
+    am.profile_begin([am.KERNEL_CLASSES.index(k) for k in ("lstm_fwd", "lstm_bwd")])
+    try:
+        got = gpu_forward_backward(m, master, x, T, B, idx, prob, lengths, h0, c0, want_state=True)
+    finally:
+        am.profile_end()
+    for k in ("lstm_fwd", "lstm_bwd"):  # (one record a layer, whatever its rounds)
+        assert am.profile_get(am.KERNEL_CLASSES.index(k))["launches"] == dims.layers
+    ref = oracle_forward_backward(dims, master, x, T, B, idx, prob, lengths, h0, c0, bf16=True)
+    _check(got, ref, dims, BF16_TOL, state=True)
+
+
 # one workgroup per 16 sequences: every width it is built for, a lone sequence,
 # a whole workgroup, one more; one step, fewer and more steps than the operand
 # ring has slots
