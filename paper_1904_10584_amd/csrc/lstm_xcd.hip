@@ -25,6 +25,15 @@
 //     of four slots in scratch memory that stays in the L2, where a value not
 //     yet written is all ones (no h is); the readers poll the rows themselves,
 //     which saves the wait for the stores, the flag's way and a second read.
+//     A slot is written anew every four steps, and whatever is not all ones is
+//     taken for the current h, so a poll must never be served from a line that
+//     this CU's L1 kept from an earlier one.  What that rests on: the ring is
+//     read by non-temporal loads alone, which leave no line in the L1 (every poll
+//     that has failed before it succeeds, of a flag or of the ring, shows it: the
+//     same address again gives the new value).  The memory model does not promise
+//     it, so the compiled polls are checked for these bits, and ring and flags
+//     are compared bit for bit, also where all four slots fit the L1 (64 and 192
+//     cells).
 // A workgroup owns U hidden units (U % 4 == 0) of one block of RB sequences
 // (RB = 16 or 32).  The forward product keeps the workgroup's 4U columns of
 // W_h resident in registers in unit-major, gate-minor order, so a 16-column
