@@ -198,6 +198,14 @@ template <int N> __device__ __forceinline__ void wait_vm_n(int n) {
   }
 }
 
+// Workgroup barrier behind every wave's LDS accesses.  Global loads and stores
+// (the direct loads in particular) stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));

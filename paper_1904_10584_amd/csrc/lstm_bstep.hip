@@ -41,12 +41,6 @@ static_assert(LOADS == 28 && (NS - 2) * LPW < 64, "memory counter");
 static_assert(2 * TM * ROWF * 4 <= LDS_BYTES, "the partial sums reuse the stages");
 static_assert(TM * TU == COMPUTE * 64 * 4, "four cells a compute thread");
 
-__device__ __forceinline__ void stage_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
@@ -93,12 +87,12 @@ __global__ __launch_bounds__(THREADS, 1) void lstm_bwd_step_fused(LstmBwdStep a,
       // stage s has landed once at most the NS - 2 later ones are in flight
       if (next - s == NS - 1) wait_vm_asm<(NS - 2) * LPW>();
       else wait_vm_asm<0>();
-      stage_barrier();
+      lds_barrier();
       issue();
     }
     if (nk > 0) {
-      stage_barrier();  // the last stage has been read
-      stage_barrier();  // the partial sums are in LDS
+      lds_barrier();  // the last stage has been read
+      lds_barrier();  // the partial sums are in LDS
     }
     return;
   }
@@ -125,7 +119,7 @@ __global__ __launch_bounds__(THREADS, 1) void lstm_bwd_step_fused(LstmBwdStep a,
     acc[0] = acc[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     auto at = [&](int r, int ks) { return r * 64 + (((ks * 4 + (lane >> 4)) ^ (r & 7)) << 3); };
     for (int s = 0; s < nk; ++s) {
-      stage_barrier();
+      lds_barrier();
       const bf16_t* la = reinterpret_cast<const bf16_t*>(lds + (s % NS) * STAGE + kh * A_HALF);
       const bf16_t* lb = reinterpret_cast<const bf16_t*>(lds + (s % NS) * STAGE + 2 * A_HALF + kh * B_HALF);
       Frag<bf16_t> af[2][2], bf[2];
@@ -140,14 +134,14 @@ __global__ __launch_bounds__(THREADS, 1) void lstm_bwd_step_fused(LstmBwdStep a,
 #pragma unroll
         for (int i = 0; i < 2; ++i) mma_16x16x32(acc[i], af[ks][i], bf[ks]);
     }
-    stage_barrier();
+    lds_barrier();
     float* part = reinterpret_cast<float*>(lds);  // [k-half][row][unit]
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         part[(kh * TM + wm + 16 * i + mfma_row(lane, r)) * ROWF + wn + mfma_col(lane)] = acc[i][r];
-    stage_barrier();
+    lds_barrier();
     if (cont) {
       const float4 p0 = *reinterpret_cast<const float4*>(part + (row - m0) * ROWF + uu - u0);
       const float4 p1 = *reinterpret_cast<const float4*>(part + (TM + row - m0) * ROWF + uu - u0);

@@ -41,14 +41,6 @@ namespace {
 
 constexpr int SEQ = 16;  // sequences per workgroup
 
-// Every wave's LDS accesses done, then the workgroup barrier.  Global loads
-// and stores (the direct loads in particular) stay in flight.
-__device__ __forceinline__ void step_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // The schedule as the waves walk it: the lengths in LDS (a vector load of one
 // would make the copying wave wait for its direct loads).
 struct Walk {
@@ -177,7 +169,7 @@ __global__ __launch_bounds__((Fwd<T, H16>::THREADS), 1) void lstm_fwd_solo(Persi
     }
     int nb = ps.B;
     for (int t = 0; t < steps; ++t) {
-      step_barrier();  // the step's projections and h_{t-1} are in LDS
+      lds_barrier();  // the step's projections and h_{t-1} are in LDS
       nb = walk.down(nb, t);
       const bool ok = b0 + seq < nb;
       const unsigned char* hin = hslot(t) + seq * F::HS + kq * 8 * E;
@@ -215,7 +207,7 @@ __global__ __launch_bounds__((Fwd<T, H16>::THREADS), 1) void lstm_fwd_solo(Persi
         }
       }
     }
-    step_barrier();
+    lds_barrier();
   } else if (wave == 8) {
     // the projections of step t + D - 1 are requested during step t
     const char* P = static_cast<const char*>(a.P);
@@ -233,16 +225,16 @@ __global__ __launch_bounds__((Fwd<T, H16>::THREADS), 1) void lstm_fwd_solo(Persi
       // step t's have landed once at most the D - 2 later steps' are in flight
       if (next - t == D - 1) wait_vm_asm<(D - 2) * F::PCopy::NI>();
       else wait_vm_asm<0>();
-      step_barrier();
+      lds_barrier();
       issue();
     }
-    step_barrier();
+    lds_barrier();
   } else {
     // the results of step t - 1 leave during step t
     const int w = wave - 9;
     int nb = ps.B, off = 0, nb_done = 0, off_done = 0;
     for (int t = 0; t <= steps; ++t) {
-      step_barrier();
+      lds_barrier();
       if (t > 0) {
         const int rows = min(SEQ, nb_done - b0);
         const int64_t r0 = off_done + b0;
@@ -334,7 +326,7 @@ __global__ __launch_bounds__((Bwd<T, H16>::THREADS), 1) void lstm_bwd_solo(Persi
     for (int r = 0; r < 4; ++r) dc[r] = 0.f;
     int nb = nb_last, nb_next = 0;
     for (int i = 0; i < steps; ++i) {
-      step_barrier();  // the step's operands and dA of the step before are in LDS
+      lds_barrier();  // the step's operands and dA of the step before are in LDS
       if (i > 0) {
         nb_next = nb;
         nb = walk.up(nb, t_last - i);
@@ -393,7 +385,7 @@ __global__ __launch_bounds__((Bwd<T, H16>::THREADS), 1) void lstm_bwd_solo(Persi
         }
       }
     }
-    step_barrier();
+    lds_barrier();
   } else if (wave == H16) {
     // gates, incoming dh and c_{t-1} of step i + D - 1, requested during step
     // i.  c_{t-1} is copied for every row active at t - 1: it is the next
@@ -419,14 +411,14 @@ __global__ __launch_bounds__((Bwd<T, H16>::THREADS), 1) void lstm_bwd_solo(Persi
     for (int i = 0; i < steps; ++i) {
       if (next - i == D - 1) wait_vm_asm<(D - 2) * F::NI>();
       else wait_vm_asm<0>();
-      step_barrier();
+      lds_barrier();
       issue();
     }
-    step_barrier();
+    lds_barrier();
   } else {
     int nb = nb_last, off = off_last;  // of step i - 1
     for (int i = 0; i <= steps; ++i) {
-      step_barrier();
+      lds_barrier();
       if (i == 0) continue;
       write_rows<4 * H * E / 16, F::AS>(static_cast<T*>(a.dA) + (int64_t)(off + b0) * 4 * H, aslot(i - 1),
                                         min(SEQ, nb - b0), 0, 1, lane);

@@ -53,13 +53,6 @@ namespace {
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
 
-// Barrier that orders LDS only: loads and stores stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // Two numbers to bf16 (round to nearest even) by the conversion instruction,
 // a at the low end.
 __device__ __forceinline__ uint32_t cvt_bf16x2(float a, float b) {
