@@ -4,7 +4,18 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "per_device.h"
+
 namespace am {
+
+// Lets kernel `fn` take `bytes` of dynamic LDS on the current device (`limit`:
+// this kernel's, set once for each device).
+inline hipError_t allow_lds(PerDevice& limit, const void* fn, int bytes) {
+  int dev = 0;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  return limit.once(dev, [&] { return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
 
 // C[M][N] = sum_k A(m,k) B(k,n) (+ bias[n]).
 //   A(m,k) = A[m*lda + k] if a_kmajor else A[k*lda + m]

@@ -623,13 +623,9 @@ template <bool AK, bool BKM, typename OutT, bool BIAS, bool ROWSUM, int BN, int 
 hipError_t launch(const GemmArgs& g, Out<OutT> dst, float* rowsum, int S, int kps, hipStream_t s) {
   auto kern = gemm_bf16_kernel<AK, BKM, OutT, BIAS, ROWSUM, BN, BM>;
   constexpr int lds = Cfg<BN, BM>::LDS;
-  static bool attr = false;  // per instantiation
-  if (!attr) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static PerDevice limit;  // per instantiation
+  const hipError_t e = allow_lds(limit, reinterpret_cast<const void*>(kern), lds);
+  if (e != hipSuccess) return e;
   const bf16_t* a = static_cast<const bf16_t*>(g.A);
   const bf16_t* b = static_cast<const bf16_t*>(g.B);
   const bf16_t* b2 = g.B2 ? static_cast<const bf16_t*>(g.B2) : b;
@@ -658,13 +654,9 @@ hipError_t launch_cell(const GemmArgs& g, const CellArgs& cell, hipStream_t s) {
   auto kern = gemm_bf16_kernel<true, true, float, false, false, T, TM, true>;
   constexpr int lds = Cfg<T, TM>::LDS;
   static_assert(TM * (T + 4) * 4 <= lds, "the cell epilogue stages the fp32 tile in LDS");
-  static bool attr = false;
-  if (!attr) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static PerDevice limit;
+  const hipError_t e = allow_lds(limit, reinterpret_cast<const void*>(kern), lds);
+  if (e != hipSuccess) return e;
   const bf16_t* a = static_cast<const bf16_t*>(g.A);
   const bf16_t* b = static_cast<const bf16_t*>(g.B);
   Op A{a, g.lda, a, g.lda, 1 << 30};

@@ -200,13 +200,9 @@ bool lstm_bwd_fused_pays(int hidden, int steps) {
 }
 
 hipError_t lstm_bwd_step_fused_launch(const LstmBwdStep& a, hipStream_t s) {
-  static bool attr = false;
-  if (!attr) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(lstm_bwd_step_fused),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static PerDevice limit;
+  const hipError_t e = allow_lds(limit, reinterpret_cast<const void*>(lstm_bwd_step_fused), LDS_BYTES);
+  if (e != hipSuccess) return e;
   const int tm = (a.nb + TM - 1) / TM, tu = (a.hidden + TU - 1) / TU;
   hipLaunchKernelGGL(lstm_bwd_step_fused, dim3(tm * tu), dim3(THREADS), LDS_BYTES, s, a, tm, tu);
   return hipGetLastError();
