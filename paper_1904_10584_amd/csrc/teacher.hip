@@ -15,10 +15,12 @@
 // entries fall into 64 or 128 groups; the k-th largest of the groups' maxima
 // is a bound that at least k entries reach and few more do.  Those entries are
 // gathered in LDS, and each lane finds the rank of its one or two of them by
-// comparing with all: the rank is the place in the output.  A row with more
-// than 128 of them (many equal values) takes k rounds of a wave-wide maximum
-// instead.  What bounds it: the vector unit's passes over the row's registers;
-// 16384 x 3000, k = 20: 110 us (k rounds for every row, loads behind branches) -> 58.
+// comparing with all: the rank is the place in the output.  Where more than 128
+// reach it, the equal values at the bound are cut to what is left to k, in order.
+// What bounds it: the vector unit's passes over the row's registers; 16384 x 3000,
+// k = 20: 93 us (k rounds for every row, loads behind branches) -> 53, rows of equal
+// values 149 -> 59.  Few k of short rows (DIRECT), and rows with more than 128
+// entries above the bound, take k rounds of a wave-wide maximum instead.
 //
 // kbest_posterior_rows: the posterior rebuilt from k stored logits with the
 // missing ones at -infinity, i.e. the softmax over the k values (fp32; sums in
@@ -88,8 +90,15 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
-template <int CPL, bool VEC>
-__global__ __launch_bounds__(256) void topk_rows_kernel(int64_t N, int C, int K,
+// Wavefronts a SIMD that the registers are to leave room for: those of the common
+// rows' passes, which the code for the rare ones would push down by one (16384 x
+// 3000, k = 20: 61 us at three, 52 at four; the rare ones spill a few registers).
+constexpr int topk_waves(int cpl, bool direct) {
+  return direct ? 1 : cpl <= 16 ? 8 : cpl <= 32 ? 5 : cpl <= 48 ? 4 : cpl <= 64 ? 3 : cpl <= 96 ? 2 : 1;
+}
+
+template <int CPL, bool VEC, bool DIRECT>
+__global__ __launch_bounds__(256, topk_waves(CPL, DIRECT)) void topk_rows_kernel(int64_t N, int C, int K,
                                                         const float* __restrict__ z,
                                                         int32_t* __restrict__ idx,
                                                         float* __restrict__ val) {
@@ -123,92 +132,133 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(int64_t N, int C, int K,
     return key[q] ? ((uint64_t)key[q] << 32) | (uint32_t)~(uint32_t)cls(q) : 0ull;
   };
 
-  // Group maxima: registers of four by four in turn, one group a lane (k <=
-  // 32: about 1.4 k entries reach the k-th largest of 64 maxima) or two.
-  __shared__ __align__(16) uint64_t scratch[4][CANDS];
-  uint64_t* mine_lds = scratch[threadIdx.x >> 6];
-  uint32_t g0 = 0, g1 = 0;
-#pragma unroll
-  for (int q = 0; q < CPL; ++q) {
-    if ((q >> 2) & 1) g1 = key[q] > g1 ? key[q] : g1;
-    else g0 = key[q] > g0 ? key[q] : g0;
-  }
-  uint32_t bound;
-  {
-    // the k-th largest: the one with k - 1 before it, equal ones in the
-    // order of their groups
-    uint32_t* gl = reinterpret_cast<uint32_t*>(mine_lds);
-    uint32_t r0 = 0, r1 = 0;
-    const bool two = K > 32;  // (uniform)
-    if (!two) g0 = g0 > g1 ? g0 : g1;
-    gl[lane] = g0;
-    gl[64 + lane] = two ? g1 : 0u;
-    wave_lds_order();
-    const uint4* gv = reinterpret_cast<const uint4*>(gl);
-    auto count = [&](uint32_t v, int at) {
-      r0 += v > g0 || (v == g0 && at < lane);
-      r1 += v > g1 || (v == g1 && at < 64 + lane);
+  if constexpr (!DIRECT) {
+    __shared__ __align__(16) uint64_t scratch[4][CANDS];
+    uint64_t* mine_lds = scratch[threadIdx.x >> 6];
+    // set bits of m below this lane's
+    auto below = [](uint64_t m) {
+      return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
     };
-    const int nv = two ? 32 : 16;
-    for (int i = 0; i < nv; i += 4) {
-      uint4 v[4];
+    // Group maxima: registers of four by four in turn, one group a lane (k <=
+    // 32: about 1.4 k entries reach the k-th largest of 64 maxima) or two.
+    uint32_t g0 = 0, g1 = 0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = gv[i + j];
+    for (int q = 0; q < CPL; ++q) {
+      if ((q >> 2) & 1) g1 = key[q] > g1 ? key[q] : g1;
+      else g0 = key[q] > g0 ? key[q] : g0;
+    }
+    uint32_t bound;
+    {
+      // the k-th largest: the one with k - 1 before it, equal ones in the
+      // order of their groups
+      uint32_t* gl = reinterpret_cast<uint32_t*>(mine_lds);
+      uint32_t r0 = 0, r1 = 0;
+      const bool two = K > 32;  // (uniform)
+      if (!two) g0 = g0 > g1 ? g0 : g1;
+      gl[lane] = g0;
+      gl[64 + lane] = two ? g1 : 0u;
+      wave_lds_order();
+      const uint4* gv = reinterpret_cast<const uint4*>(gl);
+      auto count = [&](uint32_t v, int at) {
+        r0 += v > g0 || (v == g0 && at < lane);
+        r1 += v > g1 || (v == g1 && at < 64 + lane);
+      };
+      const int nv = two ? 32 : 16;
+      for (int i = 0; i < nv; i += 4) {
+        uint4 v[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        count(v[j].x, 4 * (i + j));
-        count(v[j].y, 4 * (i + j) + 1);
-        count(v[j].z, 4 * (i + j) + 2);
-        count(v[j].w, 4 * (i + j) + 3);
+        for (int j = 0; j < 4; ++j) v[j] = gv[i + j];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          count(v[j].x, 4 * (i + j));
+          count(v[j].y, 4 * (i + j) + 1);
+          count(v[j].z, 4 * (i + j) + 2);
+          count(v[j].w, 4 * (i + j) + 3);
+        }
+      }
+      const uint64_t h0 = __ballot(r0 == (uint32_t)(K - 1)), h1 = two ? __ballot(r1 == (uint32_t)(K - 1)) : 0ull;
+      bound = h0 ? (uint32_t)__builtin_amdgcn_readlane((int)g0, __builtin_ctzll(h0))
+                 : (uint32_t)__builtin_amdgcn_readlane((int)g1, __builtin_ctzll(h1 ? h1 : 1ull));
+      wave_lds_order();
+    }
+    // (no bound where fewer than k groups hold anything: every entry counts)
+    if (bound == 0u) bound = 1u;
+    int n = 0;
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+      const uint64_t hit = __ballot(key[q] >= bound);
+      if (hit) {  // (uniform)
+        const int at = n + below(hit);
+        if (key[q] >= bound && at < CANDS) mine_lds[at] = cand(q);
+        n += __popcll(hit);
       }
     }
-    const uint64_t h0 = __ballot(r0 == (uint32_t)(K - 1)), h1 = two ? __ballot(r1 == (uint32_t)(K - 1)) : 0ull;
-    bound = h0 ? (uint32_t)__builtin_amdgcn_readlane((int)g0, __builtin_ctzll(h0))
-               : (uint32_t)__builtin_amdgcn_readlane((int)g1, __builtin_ctzll(h1 ? h1 : 1ull));
-    wave_lds_order();
-  }
-  // (no bound where fewer than k groups hold anything: every entry counts)
-  if (bound == 0u) bound = 1u;
-  int n = 0;
+    if (n > CANDS) {
+      // Equal values at the bound: those above it, then of the equal ones as many
+      // as are left to K, by ascending class.  (More than CANDS above it: rounds.)
+      int m = 0;
 #pragma unroll
-  for (int q = 0; q < CPL; ++q) {
-    const uint64_t hit = __ballot(key[q] >= bound);
-    if (hit) {  // (uniform)
-      const int at = n + __builtin_amdgcn_mbcnt_hi((uint32_t)(hit >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hit, 0));
-      if (key[q] >= bound && at < CANDS) mine_lds[at] = cand(q);
-      n += __popcll(hit);
-    }
-  }
-  if (n <= CANDS) {
-    wave_lds_order();
-    const uint64_t c0 = lane < n ? mine_lds[lane] : 0ull, c1 = 64 + lane < n ? mine_lds[64 + lane] : 0ull;
-    int r0 = 0, r1 = 0;
-    int i = 0;
-    for (; i + 4 <= n; i += 4) {
-      uint64_t v[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = mine_lds[i + j];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        r0 += v[j] > c0;
-        r1 += v[j] > c1;
+      for (int q = 0; q < CPL; ++q) {
+        const uint64_t hit = __ballot(key[q] > bound);
+        if (hit) {
+          const int at = m + below(hit);
+          if (key[q] > bound && at < CANDS) mine_lds[at] = cand(q);
+          m += __popcll(hit);
+        }
       }
+      n = m;
+      constexpr int E = VEC ? 4 : 1;  // classes of a lane side by side
+#pragma unroll
+      for (int q = 0; q < CPL; q += E)
+        if (n < K) {  // (uniform)
+          uint64_t tie[E];
+          int at = n;
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            tie[e] = __ballot(key[q + e] == bound);
+            at += below(tie[e]);
+            n += __popcll(tie[e]);
+          }
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+            if (key[q + e] == bound) {
+              if (at < K) mine_lds[at] = cand(q + e);
+              ++at;
+            }
+        }
+      if (m < K) n = K;
     }
-    for (; i < n; ++i) {
-      r0 += mine_lds[i] > c0;
-      r1 += mine_lds[i] > c1;
+    if (n <= CANDS) {
+      wave_lds_order();
+      const uint64_t c0 = lane < n ? mine_lds[lane] : 0ull, c1 = 64 + lane < n ? mine_lds[64 + lane] : 0ull;
+      int r0 = 0, r1 = 0;
+      int i = 0;
+      for (; i + 4 <= n; i += 4) {
+        uint64_t v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = mine_lds[i + j];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          r0 += v[j] > c0;
+          r1 += v[j] > c1;
+        }
+      }
+      for (; i < n; ++i) {
+        r0 += mine_lds[i] > c0;
+        r1 += mine_lds[i] > c1;
+      }
+      if (lane < n && r0 < K) {
+        const int c = (int)~(uint32_t)c0;
+        idx[row * K + r0] = c;
+        val[row * K + r0] = zr[c];  // (the value itself: signed zeros and NaN payloads)
+      }
+      if (64 + lane < n && r1 < K) {
+        const int c = (int)~(uint32_t)c1;
+        idx[row * K + r1] = c;
+        val[row * K + r1] = zr[c];
+      }
+      return;
     }
-    if (lane < n && r0 < K) {
-      const int c = (int)~(uint32_t)c0;
-      idx[row * K + r0] = c;
-      val[row * K + r0] = zr[c];  // (the value itself: signed zeros and NaN payloads)
-    }
-    if (64 + lane < n && r1 < K) {
-      const int c = (int)~(uint32_t)c1;
-      idx[row * K + r1] = c;
-      val[row * K + r1] = zr[c];
-    }
-    return;
   }
 
   // this lane's best two candidates, from one pass over its registers
@@ -321,14 +371,10 @@ hipError_t gather_rows(const GatherRows& a, bool bf16, hipStream_t s) {
   return hipGetLastError();
 }
 
-#define AM_TOPK_CASE(CPL_)                                                                    \
-  if (cpl <= CPL_) {                                                                          \
-    if (vec)                                                                                  \
-      hipLaunchKernelGGL((topk_rows_kernel<CPL_, true>), dim3((unsigned)((N + 3) / 4)),        \
-                         dim3(256), 0, s, N, C, K, z, idx, val);                               \
-    else                                                                                      \
-      hipLaunchKernelGGL((topk_rows_kernel<CPL_, false>), dim3((unsigned)((N + 3) / 4)),       \
-                         dim3(256), 0, s, N, C, K, z, idx, val);                               \
+#define AM_TOPK_CASE(CPL_, DIRECT_)                                                           \
+  if (cpl <= CPL_ && direct == DIRECT_) {                                                     \
+    auto kernel = vec ? topk_rows_kernel<CPL_, true, DIRECT_> : topk_rows_kernel<CPL_, false, DIRECT_>; \
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, s, N, C, K, z, idx, val); \
     return hipGetLastError();                                                                 \
   }
 
@@ -338,8 +384,21 @@ hipError_t topk_rows(int64_t N, int C, int K, const float* z, int32_t* idx, floa
   const int cpl = (C + 63) / 64;
   // 16-byte row loads need every row start 16-byte aligned
   const bool vec = C % 4 == 0 && (reinterpret_cast<uintptr_t>(z) & 15) == 0;
-  AM_TOPK_CASE(16) AM_TOPK_CASE(32) AM_TOPK_CASE(48) AM_TOPK_CASE(64) AM_TOPK_CASE(96)
-  AM_TOPK_CASE(128)
+  // k rounds at once where they are the faster ones: the bound costs about ten of
+  // them on rows of up to 1024 entries, six up to 2048, and is never worth it where
+  // most of a short row would reach it
+  // rounds alone for few k of short rows.  Rounds / bound, us for 32768 rows: 256
+  // entries, k = 4, 12 / 14, k = 5, 14 / 14; 512 entries, k = 8, 29 / 32, k = 10, 33 /
+  // 31; 1024, k = 10, 45 / 48, k = 12, 52 / 48; 16384 rows of 2048, k = 6, 37 / 40, k =
+  // 10, 43 / 40
+  const int few = cpl <= 4 ? 5 : cpl <= 8 ? 9 : cpl <= 12 ? 10 : cpl <= 16 ? 11 : cpl <= 32 ? 8 : 0;
+  // (rows of up to 256 entries fill C / 4 groups: fewer than k of them give no bound)
+  const bool direct = K < few || (C > CANDS && C <= 256 && 4 * K >= C);
+  AM_TOPK_CASE(4, true) AM_TOPK_CASE(8, true) AM_TOPK_CASE(12, true) AM_TOPK_CASE(16, true)
+  AM_TOPK_CASE(32, true)
+  AM_TOPK_CASE(4, false) AM_TOPK_CASE(8, false) AM_TOPK_CASE(12, false) AM_TOPK_CASE(16, false)
+  AM_TOPK_CASE(32, false) AM_TOPK_CASE(48, false) AM_TOPK_CASE(64, false) AM_TOPK_CASE(96, false)
+  AM_TOPK_CASE(128, false)
   return hipErrorInvalidValue;
 }
 

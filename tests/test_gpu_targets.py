@@ -41,6 +41,37 @@ def test_kbest_logits_bounds(C, K):
     np.testing.assert_array_equal(val.cpu().numpy().view(np.uint32), rv.astype(np.float32).view(np.uint32))
 
 
+# both sides of the lines where few k of short rows are left to rounds, and short
+# rows that nearly all reach the bound; more than 128 equal values at the bound with any
+# number above it, whole and partial blocks of registers, aligned rows or not
+@pytest.mark.parametrize("C,K", [(64, 1), (256, 4), (256, 5), (257, 8), (512, 9), (513, 9), (768, 10), (769, 10),
+                                 (1024, 11), (1025, 7), (2048, 8), (2049, 1), (200, 50), (256, 64), (640, 20), (641, 20), (3000, 20), (3001, 20), (5000, 33),
+                                 (6147, 64), (8192, 32)])
+def test_kbest_logits_routes_and_ties(C, K):
+    rng = np.random.default_rng(C * 67 + K)
+    N = 131
+    z = rng.standard_normal((N, C)).astype(np.float32)
+    for r in range(N - 40):  # equal values, r % (K + 40) larger ones, the rest below
+        above = r % (K + 40)
+        z[r] = np.float32(-r)
+        z[r, rng.permutation(C)[:C // 5]] -= 1.0
+        at = rng.permutation(C)[:above]
+        z[r, at] = rng.integers(1, 5, len(at)) if r % 2 else rng.uniform(1, 5, len(at))
+        if r % 3 == 0:
+            z[r, rng.permutation(C)[:C // 7]] = np.nan
+        if r % 7 == 0:
+            z[r] = np.where(z[r] == -r, np.float32(np.nan), z[r])
+    z[-1] = -np.inf
+    z[-2] = np.where(np.arange(C) % 2 == 1, np.float32(0.0), np.float32(-0.0))
+    say(f"kbest routes C={C} K={K}")
+    idx = torch.empty((N, K), dtype=torch.int32, device="cuda")
+    val = torch.empty((N, K), dtype=torch.float32, device="cuda")
+    am.kbest_logits(to_dev(z), idx, val)
+    ri, rv = oracle.topk_logits(z, K)
+    np.testing.assert_array_equal(idx.cpu().numpy(), ri)
+    np.testing.assert_array_equal(val.cpu().numpy().view(np.uint32), rv.astype(np.float32).view(np.uint32))
+
+
 @pytest.mark.parametrize("N,K", [(1, 1), (63, 20), (130, 64), (67, 65), (5, 1000), (3, 4096), (3, 4097)])
 def test_kbest_posterior_tiles(N, K):
     rng = np.random.default_rng(N + K)
