@@ -367,7 +367,10 @@ __global__ __launch_bounds__(TPB) void gtc_multi_bounds(const uint32_t* __restri
 // A tile's words of every stream: the streams' ranges are fetched by a lane
 // each, then a wave takes every fourth stream, the first words of four of them
 // in flight at once (walking the streams one after another, two dependent
-// loads each, took 32 us for 8 streams at 1 %; now 18).
+// loads each, took 32 us for 8 streams at 1 %; now 18).  Where the waves' shares
+// would differ, the whole workgroup takes one stream after another (24.1 M
+// elements, 1 stream of 10 % 30.6 us by a wave, 26.6 so; 5 of 25 % 58.7 and 48.7),
+// but for short ranges, whose latency counts.
 template <bool ACC, bool V4>
 __global__ __launch_bounds__(TPB) void gtc_multi_tiles(const uint32_t* __restrict__ words,
                                                        int64_t capacity,
@@ -400,6 +403,18 @@ __global__ __launch_bounds__(TPB) void gtc_multi_tiles(const uint32_t* __restric
       range[threadIdx.x] = make_int2((int)lo, (int)hi);
     }
     __syncthreads();
+    if (ns % 4 != 0) {  // (the waves' shares differ)
+      const int2 r = range[lane < ns ? lane : 0];
+      if (__any(r.y - r.x > (ns < 4 ? 64 : 512))) {  // the whole workgroup takes one stream after another
+        for (int s = 0; s < ns; ++s) {
+          const int2 rs = range[s];
+          const uint32_t* w = words + (int64_t)(s0 + s) * capacity;
+          for (int p = rs.x + threadIdx.x; p < rs.y; p += TPB) add(w[p]);
+        }
+        __syncthreads();  // (the ranges are replaced; the last time: the sums are complete)
+        continue;
+      }
+    }
     for (int q = wave; q < ns; q += 16) {
       uint32_t first[4];
       int2 r[4];

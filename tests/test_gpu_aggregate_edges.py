@@ -34,7 +34,11 @@ def _offset_dense(base, off):
 
 
 @pytest.mark.parametrize("n,S,rate", [(3, 2, 0.9), (4095, 16, 0.5), (12289, 65, 0.05), (8192, 130, 1.0),
-                                      (40_003, 17, 0.003)])
+                                      (40_003, 17, 0.003),
+                                      # waves' shares that differ: by the whole workgroup
+                                      # where a range is long, else by the waves
+                                      (12_289, 1, 0.9), (8192, 1, 0.015), (8192, 2, 0.3), (4096, 3, 0.015),
+                                      (20_000, 5, 0.5), (20_000, 6, 0.1), (9001, 67, 0.4), (9001, 69, 0.1)])
 @pytest.mark.parametrize("accumulate", [False, True])
 @pytest.mark.parametrize("off", [0, 1])
 def test_decode_multi_edges(n, S, rate, accumulate, off):
