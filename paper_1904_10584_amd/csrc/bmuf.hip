@@ -66,11 +66,12 @@ __device__ __forceinline__ void add_models(double* s, const float* m, int64_t st
 
 // Four elements a thread, the whole array in one grid (a loop over 8192
 // workgroups ended unevenly: 258 us where one grid took 239).  What bounds it:
-// HBM.  STREAM: every access non-temporal (see the launch).  24,145,848
-// elements, 8 addends, both restart copies (1.30 GB): 245 -> 216 us on one card,
-// 248 -> 229 on another; 10,000,001 elements, 3 addends, whose rows start off
-// the 16-byte grid (one element at a time before): 216 -> 59.
-template <bool STREAM>
+// HBM, or the memory-side cache.  BATCH: the models asked for eight and four at a
+// time, ahead of their adds.  STREAM: every access non-temporal (see the launch
+// for both).  24,145,848 elements, 8 addends, both restart copies (1.30 GB): 245 ->
+// 216 us on one card, 248 -> 229 on another; 10,000,001 elements, 3 addends, whose
+// rows start off the 16-byte grid (one element at a time before): 216 -> 51.
+template <bool BATCH, bool STREAM>
 __global__ __launch_bounds__(256) void bmuf_kernel(int64_t n, int count, double workers,
                                                    const float* models,
                                                    int64_t stride, float* wg, float* delta,
@@ -80,16 +81,29 @@ __global__ __launch_bounds__(256) void bmuf_kernel(int64_t n, int count, double 
   const int64_t step = (int64_t)gridDim.x * 256 * 4;
   for (int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; e < n; e += step) {
     if (e + 3 < n) {
-      const f32x4_t w4 = load4<STREAM>(wg + e), d4 = load4<STREAM>(delta + e);
       double s[4] = {0.0, 0.0, 0.0, 0.0};
       const float* m = models + e;
-      int i = 0;
-      for (; i + 8 <= count; i += 8) add_models<8, STREAM>(s, m + (int64_t)i * stride, stride);
-      if (count - i >= 4) {
-        add_models<4, STREAM>(s, m + (int64_t)i * stride, stride);
-        i += 4;
+      f32x4_t w4, d4;
+      if constexpr (BATCH) {
+        w4 = load4<STREAM>(wg + e);
+        d4 = load4<STREAM>(delta + e);
+        int i = 0;
+        for (; i + 8 <= count; i += 8) add_models<8, STREAM>(s, m + (int64_t)i * stride, stride);
+        if (count - i >= 4) {
+          add_models<4, STREAM>(s, m + (int64_t)i * stride, stride);
+          i += 4;
+        }
+        for (; i < count; ++i) add_models<1, STREAM>(s, m + (int64_t)i * stride, stride);
+      } else {
+#pragma unroll 1
+        for (int i = 0; i < count; ++i, m += stride) {
+          const f32x4_t v = load4<STREAM>(m);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) s[q] = s[q] + (double)v[q];
+        }
+        w4 = load4<STREAM>(wg + e);
+        d4 = load4<STREAM>(delta + e);
       }
-      for (; i < count; ++i) add_models<1, STREAM>(s, m + (int64_t)i * stride, stride);
       f32x4_t nw, nd;
       u16x4_t b;
 #pragma unroll
@@ -139,7 +153,13 @@ hipError_t bmuf_update(int64_t n, int count, int workers, const float* models, i
   const int64_t addends = n * 4 * (int64_t)count;
   const int64_t bytes = addends + n * (8 + 8 + (local ? 4 : 0) + (local_bf16 ? 2 : 0));
   const bool stream = addends > ((int64_t)256 << 20) || bytes > ((int64_t)544 << 20);
-  hipLaunchKernelGGL(stream ? bmuf_kernel<true> : bmuf_kernel<false>, dim3(blocks), dim3(256), 0, s, n, count,
+  // Batches of loads where memory latency is what they hide; from the cache, more
+  // waves with fewer registers do as well or better.  One at a time / batches, us:
+  // 1 M x 15 13.0 / 13.9, 2 M x 16 (149 MiB) 25.0 / 26.1, 6 M x 7 (286 MiB) 43.1 /
+  // 43.9, 6 M x 9 (332 MiB) 54.3 / 50.5, 6 M x 11 (378 MiB) 65.5 / 63.7.
+  const bool batch = stream || bytes > ((int64_t)288 << 20);
+  auto kernel = stream ? bmuf_kernel<true, true> : batch ? bmuf_kernel<true, false> : bmuf_kernel<false, false>;
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, n, count,
                      (double)workers, models, stride, wg, delta, (double)eta, (double)eta_next,
                      (double)zeta, local, local_bf16);
   return hipGetLastError();

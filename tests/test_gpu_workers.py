@@ -140,12 +140,14 @@ def test_bmuf_bit_exact(n, N, count, outputs):
 
 
 # every remainder of the batches of model loads (8, 4, 1), arrays that start
-# off the 16-byte grid, larger arrays, and sizes on both sides of the streaming
-# lines (256 MiB of addends: 16 of 4,194,304 elements; 544 MiB touched: one
-# addend, 26 bytes an element, 21,940,066 elements)
+# off the 16-byte grid, larger arrays, and sizes on both sides of the lines of
+# batched loads (288 MiB touched: nine addends, 58 bytes an element, 5,206,722
+# elements) and of streaming (256 MiB of addends: 16 of 4,194,304 elements; 544
+# MiB touched: one addend, 26 bytes an element, 21,939,436 elements)
 @pytest.mark.parametrize("n,N", [(1023, c) for c in (1, 2, 5, 7, 8, 11, 12, 13, 16)] +
                          [(3_531_985, 4), (3_531_987, 4), (3_600_002, 5),
-                          (4_194_303, 16), (4_194_307, 16), (21_940_069, 1)])
+                          (4_194_303, 16), (4_194_307, 16), (21_940_069, 1),
+                          (5_206_721, 9), (5_206_725, 9)])
 def test_bmuf_batches_and_alignment(n, N):
     say(f"bmuf n={n} N={N} offset views")
     base, models, delta = _bmuf_case(n, N, seed=2)
