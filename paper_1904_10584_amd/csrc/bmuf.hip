@@ -70,7 +70,7 @@ __device__ __forceinline__ void add_models(double* s, const float* m, int64_t st
 // time, ahead of their adds.  STREAM: every access non-temporal (see the launch
 // for both).  24,145,848 elements, 8 addends, both restart copies (1.30 GB): 245 ->
 // 216 us on one card, 248 -> 229 on another; 10,000,001 elements, 3 addends, whose
-// rows start off the 16-byte grid (one element at a time before): 216 -> 51.
+// rows start off the 16-byte grid (one element at a time before): 216 -> 52.
 template <bool BATCH, bool STREAM>
 __global__ __launch_bounds__(256) void bmuf_kernel(int64_t n, int count, double workers,
                                                    const float* models,
@@ -153,11 +153,16 @@ hipError_t bmuf_update(int64_t n, int count, int workers, const float* models, i
   const int64_t addends = n * 4 * (int64_t)count;
   const int64_t bytes = addends + n * (8 + 8 + (local ? 4 : 0) + (local_bf16 ? 2 : 0));
   const bool stream = addends > ((int64_t)256 << 20) || bytes > ((int64_t)544 << 20);
-  // Batches of loads where memory latency is what they hide; from the cache, more
-  // waves with fewer registers do as well or better.  One at a time / batches, us:
-  // 1 M x 15 13.0 / 13.9, 2 M x 16 (149 MiB) 25.0 / 26.1, 6 M x 7 (286 MiB) 43.1 /
-  // 43.9, 6 M x 9 (332 MiB) 54.3 / 50.5, 6 M x 11 (378 MiB) 65.5 / 63.7.
-  const bool batch = stream || bytes > ((int64_t)288 << 20);
+  // Batches of loads where memory latency is what they hide, and for rows off the
+  // 16-byte grid, whose accesses take two lines; from the cache, more waves with
+  // fewer registers do as well or better.  One at a time / batches, us: 1 M x 15
+  // 13.0 / 13.9, 2 M x 16 (149 MiB) 25.0 / 26.1, 6 M x 7 (286 MiB) 43.1 / 43.9, 6 M x
+  // 9 (332 MiB) 54.3 / 50.5, 6 M x 11 (378 MiB) 65.5 / 63.7; 1,000,003 x 8 12.6 /
+  // 10.8.
+  const uintptr_t off = (reinterpret_cast<uintptr_t>(models) | reinterpret_cast<uintptr_t>(wg) |
+                         reinterpret_cast<uintptr_t>(delta)) % 16;
+  const bool aligned = off == 0 && (count == 1 || stride % 4 == 0);
+  const bool batch = stream || !aligned || bytes > ((int64_t)288 << 20);
   auto kernel = stream ? bmuf_kernel<true, true> : batch ? bmuf_kernel<true, false> : bmuf_kernel<false, false>;
   hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, n, count,
                      (double)workers, models, stride, wg, delta, (double)eta, (double)eta_next,
