@@ -113,12 +113,10 @@ __global__ __launch_bounds__(256) void lfr_walk_kernel(LfrArgs a) {
 // meanwhile put chunk i + 1 (loaded four iterations before) into LDS, load
 // chunk i + 5, and evaluate and store the frames of chunk i - 1: two frames by
 // 32 dimensions at a time, four times.  Wave 5 finds where later chunks'
-// frames go (on a wave that evaluates too, that search was what the others
-// waited for: 78 us below).  What bounds it: the evaluation (two fp64
-// divisions a value, by divisors whose reciprocals are kept) and, for long
-// utterances, the walk.  128 utterances of 200-1500 frames x 192: 770 ->
-// 63 us; it was one wave per 64 dimensions that walked the frames and
-// divided as it went.
+// frames go.  What bounds it: the evaluation (two fp64 divisions a value, by
+// divisors whose reciprocals are kept) and, for long utterances, the walk.  128
+// utterances of 200-1500 frames x 192: 770 us by the kernel above, 63 by this one
+// (78 with that search on a wave that evaluates too, for which the others waited).
 constexpr int LFR_TC = 32;  // frames per chunk
 constexpr int LFR_G = 32;   // dimensions per workgroup
 constexpr int LFR_THREADS = 6 * 64;

@@ -9,8 +9,9 @@
 // compute unit's fill rate: 112 operand rows of 128 bytes per 64 k, 9 us at 64
 // bytes a clock, of which it reaches 40 %; the products are a third of that.  A
 // step of that shape takes 22.9 us instead of 27.8, and a training step of five
-// such layers over 64 x 512 frames 26.4 ms instead of 28.5.  Whole-tile waves
-// over a third of the stages each read LDS 2.6 times less and took 24.0 us.
+// such layers over 64 x 512 frames 26.4 ms instead of 28.5 on one card (26.5 to
+// 27.5 on others).  Whole-tile waves over a third of the stages each read LDS 2.6
+// times less and took 24.0 us.
 //
 // Fourteen waves.  Two copy: k-tiles of 128 as 28 direct loads of 1 KiB, half
 // each, into a ring of five LDS stages, four of them in flight; alone with

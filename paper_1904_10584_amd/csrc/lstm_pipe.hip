@@ -29,9 +29,8 @@
 // late.  Every wait is bounded, and a layer waits only for itself and the
 // layers below.
 //
-// 5 x 768, 12 sequences of 32 frames, whole forward: 468 us layer by layer ->
-// 212.  3 x 512, 48
-// chunks of 13-40 frames, whole training step: 800 -> 679 us.
+// Whole forward, layer by layer -> so: 5 x 768, 12 sequences of 32 frames 460 ->
+// 200 us; 3 x 512, 48 sequences of 40 frames 260 -> 178.
 #include <cstdlib>
 
 #include "xcd_sync.h"

@@ -63,7 +63,7 @@ def test_lfr_features_bit_exact(offset, bf16):
 
 @pytest.mark.parametrize("raw_dim", [1, 21, 22, 40])
 def test_lfr_features_chunk_edges_and_special_values(raw_dim):
-    # 32-frame chunks and 64-dimension groups with remainders on both sides,
+    # 32-frame chunks and 32-dimension groups with remainders on both sides,
     # and raw values (zeros, infinities, NaN, the largest and the smallest)
     # whose quotients leave the range the corrected division covers
     T = np.array([97, 96, 65, 64, 63, 33, 32, 31, 2, 1, 1, 0], np.int32)
